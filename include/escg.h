@@ -70,8 +70,10 @@ typedef int32_t escg_status;
 
 /* Kernel paths of a single job (escg_launch.route, escg_last_route): the
  * whole lattice in one workgroup's LDS; one tiled launch per MCS; the
- * persistent tiled kernel (all MCS in one cooperative launch, every tile
- * resident in LDS). */
+ * persistent kernels (all MCS in one cooperative launch, every part of the
+ * lattice resident in LDS: uneven patches with deep halos, or equal tiles
+ * where the launch choices name a tile shape or a workgroup size, or the
+ * patches would be too large). */
 #define ESCG_ROUTE_LDS        1u
 #define ESCG_ROUTE_TILED      2u
 #define ESCG_ROUTE_PERSISTENT 3u
@@ -85,7 +87,10 @@ typedef int32_t escg_status;
  *             (ESCG_EUNSUPPORTED, nothing enqueued, if it cannot run this
  *             job: LDS needs L <= escg_batch_max_L(S), persistent needs
  *             L % 8 == 0 and a tile plan whose tiles are all resident).
- *             Automatic: persistent if L % 8 == 0 and L >= 72, else the
+ *             Automatic: persistent if L % 8 == 0 and L >= 72, or L > 72
+ *             (not under stream capture, and not in a run until extinction
+ *             that one workgroup's LDS can hold), while the lattice fits
+ *             the LDS of all compute units; else the
  *             whole lattice in one workgroup's LDS if it fits, else one
  *             tiled launch per MCS.
  *   tile_h, tile_w   tile shape of the tiled paths (both 0: the planner's
@@ -319,7 +324,8 @@ uint32_t escg_last_route(void);
 
 /* The tile shape and workgroup size that a path would use for job p (its
  * L, S and launch choices) on the current device: persistent = 1 the
- * single-job persistent kernel, 2 a multi-job persistent launch of
+ * single-job persistent kernel with equal tiles (see ESCG_ROUTE_PERSISTENT
+ * for when it takes uneven patches instead), 2 a multi-job persistent launch of
  * escg_step_batch, 0 the per-MCS tiled kernel.  EUNSUPPORTED if that path
  * cannot run the job, EINVAL for invalid parameters, persistent > 2 or
  * NULL outputs. */

@@ -8,9 +8,10 @@ species class (S <= 7 or S > 7: the two kernel instantiations), and applied
 per call through the job's launch choices (escg.Params.with_launch).
 
 Kernels tuned:
-  persistent  the persistent tiled kernel of one large lattice: tile shape
-              (TH, TW) and workgroup size cap (threads), which together set
-              the tiles and waves per CU;
+  persistent  the persistent kernel of one large lattice: the library's own
+              choice (uneven patches, recorded with no tile shape) or equal
+              tiles of a shape (TH, TW) and workgroup size cap (threads),
+              which together set the tiles and waves per CU;
   step        the per-MCS tiled kernel (escg_step_batch with route "tiled"):
               tile shape and workgroup size cap;
   multi       the multi-job persistent kernel (escg_step_batch): the tile
@@ -158,12 +159,18 @@ def tune_tiled(torch, escg, L: int, S: int, K=None, ex: float = 1.0,
         plan = escg.tile_plan(p, kernel == "persistent")
         if plan is None or plan in seen:
             continue  # does not fit, or the same plan as another cap
-        seen.add(plan)
+        if shape is not None or kernel != "persistent":
+            seen.add(plan)
         try:
             dt = _time(lambda: escg.step_mcs(p, lat, 0, n_mcs, cnt), reps)
         except escg.EscgError:
             continue
-        results.append({"TH": plan[0], "TW": plan[1], "threads": plan[2],
+        # the library's own choice on the persistent route may be uneven
+        # patches, which no tile shape names: it is recorded as no choice
+        own = shape is None and kernel == "persistent"
+        results.append({"TH": 0 if own else plan[0],
+                        "TW": 0 if own else plan[1],
+                        "threads": 0 if own else plan[2],
                         "us_per_mcs": dt / n_mcs * 1e6,
                         "planner": shape is None})
     escg.async_status()

@@ -15,6 +15,7 @@ HEADERS = [os.path.join(CSRC, "escg_device.hpp"),
            os.path.join(CSRC, "escg_quad.hpp"),
            os.path.join(CSRC, "escg_lds.hpp"),
            os.path.join(CSRC, "escg_tile.hpp"),
+           os.path.join(CSRC, "escg_patch.hpp"),
            os.path.join(INCLUDE, "escg.h")]
 ARCH = "gfx950"
 

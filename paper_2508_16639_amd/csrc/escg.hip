@@ -10,6 +10,12 @@
 //                      workgroup barriers, counts and the stop test after
 //                      every MCS, one workgroup per job; the batch variant is
 //                      persistent and pulls jobs from a queue
+//   patch_kernel       one lattice of any even side in uneven patches, one
+//                      per CU and resident for all MCS of a call, with a halo
+//                      deep enough for several MCS between exchanges
+//   tiled_persistent_* the same with equal tiles and an exchange every MCS:
+//                      tile shapes asked for, lattices past the patch
+//                      kernel's three quads a thread, several jobs a launch
 //   tile_mcs_kernel    large lattices: one launch per MCS, each workgroup
 //                      stages a tile plus a 4-row / 8-column halo in LDS,
 //                      runs the four passes there (a 4-site halo covers the
@@ -21,6 +27,7 @@
 #include "escg_quad.hpp"
 #include "escg_lds.hpp"
 #include "escg_tile.hpp"
+#include "escg_patch.hpp"
 #include "escg.h"
 
 #include <algorithm>
@@ -692,6 +699,314 @@ __global__ __launch_bounds__(1024) void tiled_persistent_kernel(TiledArgs a)
 {
     persistent_tile<kPacked, kProb, kList>(a, xcd_tile(blockIdx.x,
                                                        a.G.TY * a.G.TX));
+}
+
+// ---------------------------------------------------------------------------
+// Patch kernel: all MCS of a lattice of any even side in one cooperative
+// launch, halos exchanged once per G.K MCS (escg_patch.hpp)
+// ---------------------------------------------------------------------------
+struct PatchArgs {
+    uint8_t *lattice;   // in/out
+    uint64_t *exch;     // exchange slot 0, slot 1 xstride words on; tags
+                        // pre-set (patch_prep_kernel)
+    uint32_t *abort;    // 1 word, zeroed
+    uint32_t *counts;   // rows (n+1)*(S+1), zeroed, or null
+    uint64_t seed;
+    PatchGeom G;
+    uint32_t S, T1, T2, replica, mcs0, n_mcs, spin_limit, moore;
+    uint32_t xstride;   // 64-bit words from exchange slot 0 to slot 1
+    uint32_t buf_bytes; // one copy of a region (patch_buffer_bytes)
+    uint32_t threads;   // updating threads
+    const uint32_t *ab; // selection thresholds (global) or null
+    uint32_t dom[32];
+};
+
+// The offsets of 64 MCS from t on, one MCS a lane: bits 2p, 2p + 1 are ox, oy
+// of pass p.  (Drawn for one MCS at a time on the scalar unit they took some
+// 70 instructions per MCS and wave, a tenth of a small patch's.)
+__device__ __forceinline__ uint32_t patch_offsets(uint32_t t,
+                                                  uint32_t replica,
+                                                  uint32_t k0, uint32_t k1)
+{
+    const Words w = philox_uniform(0u, t + (threadIdx.x & 63u),
+                                   kTagOffset << 8, replica, k0, k1);
+    return (w.w[0] & 3u) | (w.w[1] & 3u) << 2 | (w.w[2] & 3u) << 4 |
+           (w.w[3] & 3u) << 6;
+}
+
+// The count of species `sp` (per lane) from a wave's lanes' sums `pair` (two
+// 16-bit sums a dword: patch_word_sums).
+template <int NS>
+__device__ __forceinline__ uint32_t pair_sums_count(
+    const uint32_t (&pair)[NS / 2], uint32_t sp, uint32_t sites)
+{
+    uint32_t T[NS - 1];
+#pragma unroll
+    for (int k = 0; k < NS / 2; ++k) {
+        const uint32_t x = wave_sum(pair[k]);
+        T[2 * k] = k + 1 < NS / 2 ? x & 0xFFFFu : x;
+        if (2 * k + 1 < NS - 1)
+            T[2 * k + 1] = x >> 16;
+    }
+    return count_species<NS>(sp, T, sites);
+}
+
+// Halo exchange e of a patch whose region is in src (every thread of the
+// workgroup; between() as in patch_gather).
+template <class Fn>
+__device__ __forceinline__ void patch_exchange(const PatchArgs &a,
+                                               const Patch &P, uint32_t idx,
+                                               uint8_t *src,
+                                               const PatchHalo &H, uint32_t e,
+                                               uint32_t *misc, Fn &&between)
+{
+    const PatchGeom &G = a.G;
+    const uint32_t tag = exch_tag(e);
+    uint64_t *const area = a.exch + (size_t)exch_slot(e) * a.xstride;
+    patch_publish(src, area + (size_t)idx * G.slot_words, H, G, P, tag);
+    const uint32_t st = patch_gather(src, area, H, G, P, tag, a.abort,
+                                     a.spin_limit, between);
+    if (st) {
+        if (st == 2) {
+            xstore(a.abort, 1u);
+            atomicOr(&g_async_error, 1u);
+        }
+        misc[0] = 1;
+    }
+}
+
+// The MCS loop of one patch; src (shift 0) holds its region.  False if a
+// neighbour wait gave up; else the lattice is in src, with shift s.
+template <bool kPacked, bool kSeam, int kSlots, class Ctx>
+__device__ __forceinline__ bool patch_run(const PatchArgs &a, const Patch &P,
+                                          uint32_t idx, uint8_t *&src,
+                                          uint8_t *dst, uint32_t &s,
+                                          uint32_t *part, uint32_t *misc,
+                                          const Ctx &qc)
+{
+    const PatchGeom &G = a.G;
+    const uint32_t tid = threadIdx.x, S = a.S, n_mcs = a.n_mcs, K = G.K;
+    const uint32_t k0 = (uint32_t)a.seed, k1 = (uint32_t)(a.seed >> 32);
+    const uint32_t replica = a.replica, mcs0 = a.mcs0;
+    const uint32_t cdw = patch_count_dwords(kPacked);
+    uint32_t *const counts = a.counts;
+    const uint32_t gap = kSeam ? P.TH * (8 - 2 * G.part()) : 0u;
+    const uint32_t sites = P.TH * 8 * P.TQ - gap;
+    const uint32_t ns = count_states(S);
+    const PatchHalo H = patch_halo(G, P);
+    const bool counter = blockDim.x > a.threads; // a wave that only counts
+
+    if (counter && tid >= a.threads) {
+        // meets every barrier of the updating waves below; the lattice is
+        // in the same copy before every MCS
+        const PatchWords W = patch_words(G, P);
+        // The counts of R = 64 / (S + 1) rows gather in the lanes (lane
+        // slot * (S + 1) + species) and go out in one atomic of adjacent
+        // words, patches taking turns: a row at a time, the 256 patches'
+        // adds to one line cost 0.5 us per MCS at L = 512 (of 2.5).
+        const uint32_t lane = tid & 63u, W1 = S + 1, R = 64u / W1;
+        const uint32_t at = lane / W1, sp = lane - at * W1;
+        uint32_t slot = idx % R, acc = 0;
+        uint32_t p4[2], p6[3], p8[4];
+        const auto sums = [&](const PatchCounted &c, auto stage) {
+            constexpr uint32_t st = decltype(stage)::value;
+            if (64 * kCountStage * st >= W.n)
+                return;
+            if constexpr (kPacked) {
+                if (ns == 4)
+                    patch_word_sums<4, st>(c, p4);
+                else if (ns == 6)
+                    patch_word_sums<6, st>(c, p6);
+                else
+                    patch_word_sums<8, st>(c, p8);
+            } else {
+                uint32_t *const h = part + (tid & (kCountSlots - 1));
+#pragma unroll
+                for (uint32_t k = st * kCountStage; k < (st + 1) * kCountStage;
+                     ++k)
+                    if (64u * k < W.n && W.at[k] != ~0u)
+                        patch_hist_word(c.v[k], h);
+            }
+        };
+        const std::integral_constant<uint32_t, 0> stage0;
+        const std::integral_constant<uint32_t, 1> stage1;
+        const auto clear = [&] {
+            p4[0] = p4[1] = p6[0] = p6[1] = p6[2] = 0;
+            p8[0] = p8[1] = p8[2] = p8[3] = 0;
+        };
+        const auto add = [&](uint32_t row) {
+            uint32_t n;
+            if constexpr (kPacked) {
+                n = ns == 4   ? pair_sums_count<4>(p4, sp, sites)
+                    : ns == 6 ? pair_sums_count<6>(p6, sp, sites)
+                              : pair_sums_count<8>(p8, sp, sites);
+            } else { // one wave's LDS accesses run in order
+                const uint32_t x = patch_hist_sum(part, lane, gap);
+                n = (uint32_t)__builtin_amdgcn_ds_bpermute(8 * (int)sp,
+                                                           (int)x);
+            }
+            acc = at == slot ? n : acc;
+            if (++slot == R || row == n_mcs) {
+                // lane's row: row - (slot - 1) + at, if it is one of these
+                if (acc && at < slot && row + 1 + at >= slot)
+                    atomicAdd(counts + (size_t)(row + 1 + at - slot) * W1 +
+                                  sp,
+                              acc);
+                acc = 0;
+                slot = 0;
+            }
+        };
+        for (uint32_t t = 0, e = 1; t < n_mcs; ++e) {
+            const uint32_t n = min(K, n_mcs - t);
+            for (uint32_t m = 0; m < n; ++m) {
+                const PatchCounted c = patch_read_words(src, W);
+                clear();
+                __syncthreads();
+                sums(c, stage0);
+                __syncthreads();
+                sums(c, stage1);
+                __syncthreads();
+                add(t + m);
+                __syncthreads();
+            }
+            t += n;
+            if (t < n_mcs)
+                patch_exchange(a, P, idx, src, H, e, misc, [] {});
+            __syncthreads();
+            if (misc[0])
+                return false;
+        }
+        const PatchCounted c = patch_read_words(src, W);
+        clear();
+        sums(c, stage0);
+        sums(c, stage1);
+        add(n_mcs);
+        return true;
+    }
+
+    const PatchList<kSlots> T = patch_list<kSlots>(G, P, a.threads);
+    const PatchCount C = patch_count_plan(G, P);
+    // counts by the updating waves: sums into the slots in the first pass
+    // after an MCS (the last one's while the halo is on its way), flushed
+    // after the exchange
+    const auto count = [&](uint32_t m) {
+        if (!counts || counter)
+            return;
+        uint32_t *const slots = part + m * cdw;
+        if constexpr (kPacked) {
+            if (ns == 4)
+                patch_count_sums<4>(src, C, P.TH, slots);
+            else if (ns == 6)
+                patch_count_sums<6>(src, C, P.TH, slots);
+            else
+                patch_count_sums<8>(src, C, P.TH, slots);
+        } else {
+            patch_count_hist(src, C, P.TH, slots);
+        }
+    };
+    const auto flush = [&](uint32_t n, uint32_t row) { // n MCS, from row
+        if (counts && !counter)
+            for (uint32_t m = tid >> 6; m < n; m += blockDim.x >> 6)
+                patch_count_flush<kPacked>(
+                    part + m * cdw, S, sites, gap,
+                    counts + (size_t)(row + m) * (S + 1));
+    };
+    if (counts && !counter) {
+        count(0);
+        __syncthreads();
+        flush(1, 0); // the slots are next used four barriers on
+    }
+    uint32_t offs = 0;
+    Words rf = philox(T.c0[0], mcs0, kTagPass << 8, replica, k0, k1);
+    QuadSel sf = quad_sel(rf, qc);
+    for (uint32_t t = 0, e = 1; t < n_mcs; ++e) {
+        const uint32_t n = min(K, n_mcs - t);
+#pragma unroll 1
+        for (uint32_t m = 0; m < n; ++m) {
+            const uint32_t mt = mcs0 + t + m;
+            if (((t + m) & 63u) == 0)
+                offs = patch_offsets(mt, replica, k0, k1);
+            const uint32_t off =
+                __builtin_amdgcn_readlane((int)offs, (t + m) & 63u);
+            if (m > 0)
+                count(m - 1);
+#pragma unroll
+            for (uint32_t p = 0; p < 4; ++p) {
+                const uint32_t w = off >> (2 * p);
+                const PassIndex nx = p < 3 ? PassIndex{mt, p + 1}
+                                           : PassIndex{mt + 1, 0u};
+                patch_pass<kSeam>(src, dst, s, P, T, w, PassIndex{mt, p}, nx,
+                                  replica, k0, k1, qc, rf, sf);
+                uint8_t *const x = src;
+                src = dst;
+                dst = x;
+                s = w & 1u;
+                __syncthreads();
+            }
+        }
+        t += n;
+        if (t < n_mcs)
+            patch_exchange(a, P, idx, src, H, e, misc,
+                           [&] { count(n - 1); });
+        else
+            count(n - 1);
+        __syncthreads();
+        flush(n, t - n + 1);
+        if (misc[0])
+            return false;
+    }
+    return true;
+}
+
+// Dynamic LDS: count slots of K MCS, then the two copies of the region.
+// blockDim: a.threads, and a wave more if one is to count.
+template <bool kPacked, bool kProb, int kSlots>
+__global__ __launch_bounds__(1024) void patch_kernel(PatchArgs a)
+{
+    extern __shared__ __align__(16) uint8_t smem[];
+    __shared__ LdsTables<kPacked ? 8 : 32> TB;
+    const PatchGeom &G = a.G;
+    const uint32_t idx = xcd_tile(blockIdx.x, G.PY * G.PX);
+    const Patch P = patch_of(G, idx);
+    const uint32_t cdw = patch_count_dwords(kPacked);
+    uint32_t *const part = reinterpret_cast<uint32_t *>(smem);
+    uint8_t *src = smem + G.K * cdw * 4 + 8;
+    for (uint32_t i = threadIdx.x; i < G.K * cdw + a.buf_bytes / 2;
+         i += blockDim.x)
+        part[i] = 0;
+    if (threadIdx.x == 0)
+        TB.misc[0] = 0;
+    __syncthreads();
+    patch_load(src, a.lattice, G, P);
+    setup_tables(TB, a.dom, a.moore != 0, kProb ? a.ab : nullptr);
+    const auto qc = make_quad_ctx<kProb>(TB, a.T1, a.T2); // after a barrier
+    uint32_t s = 0;
+    uint8_t *const dst = src + a.buf_bytes;
+    const bool ok =
+        P.seam != ~0u
+            ? patch_run<kPacked, true, kSlots>(a, P, idx, src, dst, s, part,
+                                               TB.misc, qc)
+            : patch_run<kPacked, false, kSlots>(a, P, idx, src, dst, s, part,
+                                                TB.misc, qc);
+    if (ok && threadIdx.x < a.threads)
+        patch_store(src, s, a.lattice, G, P, a.threads);
+}
+
+// What a patch launch needs set: exchange slot 0 tagged 0, slot 1 tagged 1
+// (neither matches its first use), the abort words and the count rows 0.
+__global__ void patch_prep_kernel(uint32_t *exch, uint32_t slot_dwords,
+                                  uint32_t *abort, uint32_t *counts,
+                                  size_t n_counts)
+{
+    const size_t step = (size_t)gridDim.x * blockDim.x;
+    const size_t i0 = blockIdx.x * (size_t)blockDim.x + threadIdx.x;
+    for (size_t i = i0; i < 2 * (size_t)slot_dwords; i += step)
+        exch[i] = i < slot_dwords ? exch_tag(2) ^ 0x80808080u
+                                  : exch_tag(1) ^ 0x80808080u;
+    for (size_t i = i0; i < n_counts; i += step)
+        counts[i] = 0;
+    if (i0 == 0)
+        abort[0] = 0;
 }
 
 // Several large lattices in one launch: job j owns workgroups
@@ -1383,8 +1698,8 @@ uint32_t tiled_threads(const TileGeom &G, uint32_t cap)
     return nt;
 }
 
-// Automatic routing sends a single job with L % 8 == 0 to the persistent
-// kernel from this side on.
+// Automatic routing sends a single job to the persistent path from this side
+// on.
 constexpr uint32_t kPersistentMinL = 72;
 
 
@@ -1662,6 +1977,252 @@ escg_status run_tiled_persistent(const escg_params *p, const Derived &d,
     return s;
 }
 
+// ---------------------------------------------------------------------------
+// Patch kernel: plan and launch
+// ---------------------------------------------------------------------------
+struct PatchPlan {
+    bool ok = false;
+    PatchGeom G{};
+    uint32_t threads = 0;   // updating threads
+    uint32_t slots = 0;     // quads per thread and pass
+    bool counter = false;   // counts: by a wave of their own
+    uint32_t buf_bytes = 0; // one copy of a region
+    size_t lds = 0;         // dynamic LDS
+};
+
+constexpr uint32_t kPatchSlots = 3;
+
+const void *patch_kernel_fn(bool packed, bool prob, uint32_t slots)
+{
+#define ESCG_PATCH(S)                                                         \
+    {(const void *)patch_kernel<false, false, S>,                             \
+     (const void *)patch_kernel<false, true, S>,                              \
+     (const void *)patch_kernel<true, false, S>,                              \
+     (const void *)patch_kernel<true, true, S>}
+    static const void *const fns[kPatchSlots][4] = {
+        ESCG_PATCH(1), ESCG_PATCH(2), ESCG_PATCH(3)};
+#undef ESCG_PATCH
+    return fns[slots - 1][(packed ? 2 : 0) | (prob ? 1 : 0)];
+}
+
+// Quads of a pass on the busiest SIMD, in wave iterations: nq quads dealt in
+// turn to the waves of nt threads, the waves in turn to the four SIMDs.
+uint32_t list_simd_load(uint32_t nq, uint32_t nt)
+{
+    uint32_t simd[4] = {0, 0, 0, 0};
+    for (uint32_t t = 0; t < nt; t += 64)
+        simd[(t / 64) & 3u] += t < nq ? (nq - t + nt - 1) / nt : 0u;
+    return std::max(std::max(simd[0], simd[1]), std::max(simd[2], simd[3]));
+}
+
+PatchPlan plan_patch_uncached(uint32_t L, uint32_t S)
+{
+    PatchPlan best;
+    const DeviceInfo di = device_info();
+    const uint32_t cus = (uint32_t)std::max(1, di.cus);
+    const size_t lds_max = di.lds_max ? di.lds_max : 65536;
+    const bool packed = S <= 7;
+    const size_t fixed = static_lds_bytes(S) + 64;
+    double best_cost = 1e300;
+    PatchGeom G{};
+    G.L = L;
+    const uint32_t Lb = G.Lb(), Q = G.Q(), part = G.part();
+    for (uint32_t K = 1; K <= 7; ++K) {
+        G.K = K;
+        G.HQ = (4 * K + 1 + 7) / 8;
+        for (uint32_t PX = 1; PX <= std::min(Q, cus); ++PX) {
+            // strips come from the next patch alone, and the partial quad
+            // keeps out of every halo
+            const uint32_t tq = Q / PX, TQ = (Q + PX - 1) / PX;
+            if (tq < G.HQ || (part && tq < 2 * G.HQ + 1))
+                continue;
+            for (uint32_t PY = 1; PY <= std::min(Lb, cus / PX); ++PY) {
+                const uint32_t th = 2 * (Lb / PY);
+                const uint32_t TH = 2 * ((Lb + PY - 1) / PY);
+                if (th < G.HR())
+                    continue;
+                const uint32_t nq = (TH / 2 + G.HR()) * (TQ + 2 * G.HQ);
+                if (nq > 1024 * kPatchSlots)
+                    continue;
+                // one quad per thread, or the workgroup size with the least
+                // load of the busiest SIMD (ties: more waves)
+                uint32_t nt = std::max(64u, (nq + 63) / 64 * 64), w = nt;
+                if (nt <= 1024) {
+                    w = (nt / 64 + 3) / 4;
+                } else {
+                    for (uint32_t n = 1024; n * kPatchSlots >= nq; n -= 64) {
+                        const uint32_t l = list_simd_load(nq, n);
+                        if (l < w) {
+                            w = l;
+                            nt = n;
+                        }
+                    }
+                }
+                const uint32_t slots = (nq + nt - 1) / nt;
+                if (TQ > nt)
+                    continue;
+                const uint32_t buf = (TH + 2 * G.HR() + 1) *
+                                         (8 * (TQ + 2 * G.HQ) + 8) + 8;
+                const size_t lds =
+                    (size_t)K * patch_count_dwords(packed) * 4 +
+                    2 * (size_t)buf;
+                if (lds + fixed > lds_max)
+                    continue;
+                // us per MCS: four passes, by latency up to two waves a
+                // SIMD (1.66 and 1.95 measured at L = 512) and by issue
+                // from three on (3.15 with four at L = 1600), and the
+                // share of an exchange (0.96)
+                const double cost = std::max(1.36 + 0.30 * w,
+                                             0.30 + 0.72 * w) + 0.96 / K;
+                if (cost < best_cost) {
+                    best_cost = cost;
+                    best.ok = true;
+                    best.G = G;
+                    best.G.PX = PX;
+                    best.G.PY = PY;
+                    best.threads = nt;
+                    best.slots = slots;
+                    best.buf_bytes = buf;
+                    best.lds = lds;
+                    // a histogram's words cost 24 instructions each:
+                    // two stages of them outlast a pass
+                    best.counter =
+                        TH * TQ <= 64 * (packed ? kCountWords : kCountStage) &&
+                        nt + 64 <= 1024;
+                }
+            }
+        }
+    }
+    if (!best.ok)
+        return best;
+    if (part) { // the partial quad in the middle of patch column 0
+        const uint32_t at = best.G.col_cut(1) / 2;
+        best.G.rot = (2 * Q - 1 - at) % Q;
+    }
+    best.G.slot_words = patch_slot_words(
+        2 * ((Lb + best.G.PY - 1) / best.G.PY),
+        (Q + best.G.PX - 1) / best.G.PX, best.G.HR(), best.G.HQ);
+    for (int prob = 0; prob < 2; ++prob) { // all patches resident, one per CU
+        const void *fn = patch_kernel_fn(packed, prob != 0, best.slots);
+        allow_dynamic_lds(fn, best.lds);
+        int per_cu = 0;
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(
+                &per_cu, fn, (int)best.threads + (best.counter ? 64 : 0),
+                best.lds) != hipSuccess)
+            (void)hipGetLastError();
+        if (per_cu < 1)
+            best.ok = false;
+    }
+    return best;
+}
+
+PatchPlan plan_patch(uint32_t L, uint32_t S)
+{
+    static std::mutex mu;
+    static std::map<std::tuple<int, uint32_t, bool>, PatchPlan> cache;
+    int dev = 0;
+    (void)hipGetDevice(&dev);
+    const auto key = std::make_tuple(dev, L, S <= 7);
+    {
+        std::lock_guard<std::mutex> lk(mu);
+        auto it = cache.find(key);
+        if (it != cache.end())
+            return it->second;
+    }
+    const PatchPlan plan = plan_patch_uncached(L, S <= 7 ? 7u : 31u);
+    std::lock_guard<std::mutex> lk(mu);
+    cache[key] = plan;
+    return plan;
+}
+
+// Scratch of a patch launch: two exchange slots per patch and the abort word.
+size_t patch_scratch_bytes(const PatchPlan &plan)
+{
+    const PatchGeom &G = plan.G;
+    return 2 * (size_t)G.PY * G.PX * G.slot_words * 8 + 256;
+}
+
+// n_mcs > 0 MCS with the patch kernel; counts: every row, row 0 included.
+// area: patch_scratch_bytes(plan).  As run_tiled_persistent otherwise.
+escg_status run_patch(const escg_params *p, const Derived &d,
+                      const PatchPlan &plan, uint8_t *lattice, uint32_t mcs0,
+                      uint32_t n_mcs, uint32_t *counts, hipStream_t st,
+                      uint8_t *area, uint32_t *abort_out = nullptr)
+{
+    const PatchGeom &G = plan.G;
+    const uint32_t T = G.PY * G.PX;
+    PatchArgs a;
+    std::memset(&a, 0, sizeof(a));
+    a.lattice = lattice;
+    a.exch = reinterpret_cast<uint64_t *>(area);
+    a.xstride = T * G.slot_words;
+    a.abort = reinterpret_cast<uint32_t *>(a.exch + 2 * (size_t)a.xstride);
+    a.counts = counts;
+    a.seed = p->seed;
+    a.G = G;
+    a.S = p->S;
+    a.T1 = d.T1;
+    a.T2 = d.T2;
+    a.replica = p->replica;
+    a.mcs0 = mcs0;
+    a.n_mcs = n_mcs;
+    a.spin_limit = 1u << 22; // polls (seconds), then abort with an error
+    a.moore = (p->flags & ESCG_FLAG_MOORE) ? 1u : 0u;
+    a.buf_bytes = plan.buf_bytes;
+    a.threads = plan.threads;
+    a.ab = d.d_ab;
+    for (int i = 0; i < 32; ++i)
+        a.dom[i] = p->dom[i];
+    const size_t n_counts = counts ? (size_t)(n_mcs + 1) * (p->S + 1) : 0;
+    const size_t words = std::max<size_t>(4 * (size_t)a.xstride, n_counts);
+    const uint32_t blocks =
+        (uint32_t)std::max<size_t>(1, std::min<size_t>(512, (words + 255) / 256));
+    hipLaunchKernelGGL(patch_prep_kernel, dim3(blocks), dim3(256), 0, st,
+                       reinterpret_cast<uint32_t *>(a.exch), 2 * a.xstride,
+                       a.abort, counts, n_counts);
+    void *args[] = {&a};
+    const void *fn = patch_kernel_fn(d.small, d.prob, plan.slots);
+    allow_dynamic_lds(fn, plan.lds);
+    const uint32_t nt = plan.threads + (counts && plan.counter ? 64 : 0);
+    const hipError_t e = hipLaunchCooperativeKernel(
+        fn, dim3(T), dim3(nt), args, (unsigned)plan.lds, st);
+    if (e != hipSuccess) {
+        std::snprintf(g_last_error, sizeof(g_last_error),
+                      "cooperative launch of %u x %u refused: %s", T, nt,
+                      hipGetErrorName(e));
+        (void)hipGetLastError();
+        return ESCG_EUNSUPPORTED;
+    }
+    if (abort_out)
+        launch_copy(reinterpret_cast<uint8_t *>(abort_out),
+                    reinterpret_cast<const uint8_t *>(a.abort), 4, st);
+    return ESCG_OK;
+}
+
+// The persistent path of a job: patches unless its launch choices name a
+// tile shape or a workgroup size; then, or without a patch plan, equal tiles
+// (L % 8 == 0).
+struct ResidentPlan {
+    PatchPlan patch;
+    TiledPlan tiled;
+    bool ok() const { return patch.ok || tiled.ok; }
+    size_t scratch_bytes() const
+    {
+        return patch.ok ? patch_scratch_bytes(patch) : exchange_bytes(tiled);
+    }
+};
+
+ResidentPlan plan_resident(const escg_params *p)
+{
+    ResidentPlan r;
+    const escg_launch &ln = p->launch;
+    if (ln.tile_h == 0 && ln.threads == 0)
+        r.patch = plan_patch(p->L, p->S);
+    if (!r.patch.ok && (p->L & 7u) == 0)
+        r.tiled = plan_tiled(p->L, p->S, plan_hints(p));
+    return r;
+}
+
 // Run-until on the persistent kernel: chunks of MCS with per-MCS counts;
 // after each chunk the host reads the counts and finds the first MCS that
 // meets the stop condition; if it lies inside the chunk, the chunk is re-run
@@ -1675,8 +2236,8 @@ escg_status run_until_persistent(const escg_params *p, const Derived &d,
 {
     const uint32_t L = p->L, S = p->S, N = L * L, W = S + 1;
     const uint32_t chunk_max = 1024;
-    const TiledPlan plan = plan_tiled(L, S, plan_hints(p));
-    if (!plan.ok)
+    const ResidentPlan plan = plan_resident(p);
+    if (!plan.ok())
         return ESCG_EUNSUPPORTED;
     // counts of a chunk, then the launches' abort words, then the saved
     // lattice, then the exchange area
@@ -1684,7 +2245,7 @@ escg_status run_until_persistent(const escg_params *p, const Derived &d,
     const size_t lat_off = (cnt_bytes + 8 + 255) & ~(size_t)255;
     const size_t ex_off = (lat_off + N + 255) & ~(size_t)255;
     uint8_t *scr = nullptr;
-    if (hipMallocAsync((void **)&scr, ex_off + exchange_bytes(plan), st) !=
+    if (hipMallocAsync((void **)&scr, ex_off + plan.scratch_bytes(), st) !=
         hipSuccess)
         return ESCG_ENOMEM;
     uint32_t *cnt = reinterpret_cast<uint32_t *>(scr);
@@ -1721,6 +2282,15 @@ escg_status run_until_persistent(const escg_params *p, const Derived &d,
                       "in MCS %u..%u", from, from + n - 1);
         return ESCG_ETIMEOUT;
     };
+    auto advance = [&](uint32_t from, uint32_t n, uint32_t *rows,
+                       uint32_t *aword) {
+        return plan.patch.ok
+                   ? run_patch(p, d, plan.patch, lattice, mcs0 + from, n,
+                               rows, st, area, aword)
+                   : run_tiled_persistent(p, d, plan.tiled, lattice,
+                                          mcs0 + from, n, rows, st, area,
+                                          aword);
+    };
     // the input state
     launch_fill(cnt, W, 0, st);
     launch_fill(abort_w, 2, 0, st);
@@ -1737,8 +2307,7 @@ escg_status run_until_persistent(const escg_params *p, const Derived &d,
     while (s == ESCG_OK && t < max_mcs) {
         const uint32_t n = std::min(chunk, max_mcs - t);
         launch_copy(saved, lattice, N, st);
-        s = run_tiled_persistent(p, d, plan, lattice, mcs0 + t, n, cnt, st,
-                                 area, abort_w);
+        s = advance(t, n, cnt, abort_w);
         if (s != ESCG_OK)
             break; // EUNSUPPORTED on the first chunk: the caller falls back
         if (!fetch(n + 1)) {
@@ -1758,8 +2327,7 @@ escg_status run_until_persistent(const escg_params *p, const Derived &d,
         if (hit) {
             if (hit < n) {
                 launch_copy(lattice, saved, N, st);
-                s = run_tiled_persistent(p, d, plan, lattice, mcs0 + t, hit,
-                                         nullptr, st, area, abort_w + 1);
+                s = advance(t, hit, nullptr, abort_w + 1);
                 if (s != ESCG_OK)
                     break;
                 if (!fetch(0)) {
@@ -2072,17 +2640,30 @@ escg_status step_batch_persistent(uint32_t n, const escg_params *P,
 }
 
 // The path of a single job (escg_step_mcs, escg_run_until_extinction) from
-// its launch choice: forced, or automatic (persistent for L % 8 == 0 and
-// L >= kPersistentMinL when a resident plan exists, else the whole lattice
-// in one workgroup's LDS when it fits, else per-MCS tiled launches).
+// its launch choice: forced, or automatic (persistent for L >=
+// kPersistentMinL when a resident plan exists, else the whole lattice in one
+// workgroup's LDS when it fits, else per-MCS tiled launches).  Forcing the
+// persistent path needs L % 8 == 0.  A lattice with L % 8 != 0 keeps to
+// ordinary launches under stream capture (a cooperative one may refuse it),
+// and, where it fits the LDS, in a run until extinction (`until`), which is
+// asynchronous there.  At L = 90 a patch MCS takes 2.1 us and the LDS
+// kernel's 7.7, at L = 300 2.1 and 39.
 enum class Route { kLds, kTiled, kPersistent, kUnsupported };
 
-Route choose_route(const escg_params *p)
+Route choose_route(const escg_params *p, hipStream_t st, bool until)
 {
     const uint32_t L = p->L, S = p->S;
     const bool fits_lds = L <= lds_max_L(S);
     const auto plan_ok = [&] {
-        return (L & 7u) == 0 && plan_tiled(L, S, plan_hints(p)).ok;
+        return (L & 7u) == 0 && plan_resident(p).ok();
+    };
+    const auto ragged_ok = [&] {
+        if (L < kPersistentMinL || (until && fits_lds))
+            return false;
+        hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+        if (hipStreamIsCapturing(st, &cs) != hipSuccess)
+            (void)hipGetLastError();
+        return cs == hipStreamCaptureStatusNone && plan_resident(p).ok();
     };
     switch (p->launch.route) {
     case ESCG_ROUTE_LDS:
@@ -2092,7 +2673,7 @@ Route choose_route(const escg_params *p)
     case ESCG_ROUTE_PERSISTENT:
         return plan_ok() ? Route::kPersistent : Route::kUnsupported;
     default:
-        if ((L & 7u) == 0 && L >= kPersistentMinL && plan_ok())
+        if ((L & 7u) == 0 ? L >= kPersistentMinL && plan_ok() : ragged_ok())
             return Route::kPersistent;
         return fits_lds ? Route::kLds : Route::kTiled;
     }
@@ -2217,19 +2798,18 @@ escg_status step_mcs(const escg_params *p, uint8_t *d_lattice, uint32_t mcs0,
     hipStream_t st = ar.st;
     Derived d = derive(p);
     const uint32_t L = p->L, S = p->S, N = L * L;
-    const Route r = choose_route(p);
+    const Route r = choose_route(p, st, false);
     if (r == Route::kUnsupported)
         return ESCG_EUNSUPPORTED;
     const bool persistent = r == Route::kPersistent;
-    const TiledPlan plan =
-        persistent ? plan_tiled(L, S, plan_hints(p)) : TiledPlan{};
+    const ResidentPlan plan = persistent ? plan_resident(p) : ResidentPlan{};
     if (ar.base) {
         const size_t ab = d.prob ? Arena::round(d.ab.size() * 4) : 0;
         const size_t rest =
             r == Route::kLds ? 0
                              : Arena::round(persistent
                                                 ? std::max<size_t>(
-                                                      exchange_bytes(plan), N)
+                                                      plan.scratch_bytes(), N)
                                                 : N);
         if (n_mcs > 0 && ab + rest > ar.cap) {
             std::snprintf(g_last_error, sizeof(g_last_error),
@@ -2243,15 +2823,25 @@ escg_status step_mcs(const escg_params *p, uint8_t *d_lattice, uint32_t mcs0,
         if (s != ESCG_OK)
             return s;
     }
-    if (r == Route::kLds) {
+    const auto in_lds = [&] {
         JobDev J = make_job(p, d, 0, mcs0, n_mcs, ESCG_STOP_NONE, 0, d_counts,
                             nullptr, 0);
         g_last_route = ESCG_ROUTE_LDS;
         return launch_lds_single(J, d.small, d_lattice, st);
-    }
-    if (d_counts) {
+    };
+    if (r == Route::kLds)
+        return in_lds();
+    // a lattice with L % 8 != 0 that the LDS holds needs no scratch there
+    const bool lds_too = (L & 7u) != 0 && L <= lds_max_L(S) && persistent;
+    const bool patch = persistent && plan.patch.ok && n_mcs > 0;
+    const auto row0 = [&] { // rows zeroed, row 0 counted
+        if (!d_counts)
+            return ESCG_OK;
         launch_fill(d_counts, (size_t)(n_mcs + 1) * (S + 1), 0, st);
-        s = launch_densities(d_lattice, N, S, d_counts, st);
+        return launch_densities(d_lattice, N, S, d_counts, st);
+    };
+    if (!patch) { // the patch kernel writes every row itself
+        s = row0();
         if (s != ESCG_OK)
             return s;
     }
@@ -2260,18 +2850,26 @@ escg_status step_mcs(const escg_params *p, uint8_t *d_lattice, uint32_t mcs0,
     // one span serves the exchange area or, if the cooperative launch is
     // refused, the ping-pong lattice of the per-MCS launches
     void *span = nullptr;
-    s = ar.take(persistent ? std::max<size_t>(exchange_bytes(plan), N) : N,
+    s = ar.take(persistent ? std::max<size_t>(plan.scratch_bytes(), N) : N,
                 &span);
     if (s != ESCG_OK)
-        return s;
+        return lds_too ? in_lds() : s;
     if (persistent) {
-        s = run_tiled_persistent(p, d, plan, d_lattice, mcs0, n_mcs, d_counts,
-                                 st, static_cast<uint8_t *>(span));
+        uint8_t *const area = static_cast<uint8_t *>(span);
+        s = patch ? run_patch(p, d, plan.patch, d_lattice, mcs0, n_mcs,
+                              d_counts, st, area)
+                  : run_tiled_persistent(p, d, plan.tiled, d_lattice, mcs0,
+                                         n_mcs, d_counts, st, area);
         if (s != ESCG_EUNSUPPORTED) {
             g_last_route = ESCG_ROUTE_PERSISTENT;
             return s;
         }
-        s = ESCG_OK; // refused at launch: one tiled launch per MCS instead
+        // refused at launch: ordinary launches instead
+        if (lds_too)
+            return in_lds();
+        s = patch ? row0() : ESCG_OK;
+        if (s != ESCG_OK)
+            return s;
     }
     g_last_route = ESCG_ROUTE_TILED;
     uint8_t *other = static_cast<uint8_t *>(span);
@@ -2345,7 +2943,7 @@ escg_status escg_run_until_extinction(const escg_params *p, uint8_t *d_lattice,
             return s;
     }
     const uint32_t L = p->L, S = p->S, N = L * L;
-    const Route r = choose_route(p);
+    const Route r = choose_route(p, st, true);
     if (r == Route::kUnsupported)
         return ESCG_EUNSUPPORTED;
     if (r == Route::kPersistent) {
