@@ -87,7 +87,7 @@ typedef int32_t escg_status;
  *             (ESCG_EUNSUPPORTED, nothing enqueued, if it cannot run this
  *             job: LDS needs L <= escg_batch_max_L(S), persistent needs
  *             L % 8 == 0 and a tile plan whose tiles are all resident).
- *             Automatic: persistent if L % 8 == 0 and L >= 72, or L > 72
+ *             Automatic: persistent if L % 8 == 0 and L >= 72, or L > 88
  *             (not under stream capture, and not in a run until extinction
  *             that one workgroup's LDS can hold), while the lattice fits
  *             the LDS of all compute units; else the

@@ -16,6 +16,7 @@ HEADERS = [os.path.join(CSRC, "escg_device.hpp"),
            os.path.join(CSRC, "escg_lds.hpp"),
            os.path.join(CSRC, "escg_tile.hpp"),
            os.path.join(CSRC, "escg_patch.hpp"),
+           os.path.join(CSRC, "escg_whole.hpp"),
            os.path.join(INCLUDE, "escg.h")]
 ARCH = "gfx950"
 

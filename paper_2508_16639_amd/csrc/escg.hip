@@ -28,6 +28,7 @@
 #include "escg_lds.hpp"
 #include "escg_tile.hpp"
 #include "escg_patch.hpp"
+#include "escg_whole.hpp"
 #include "escg.h"
 
 #include <algorithm>
@@ -992,6 +993,158 @@ __global__ __launch_bounds__(1024) void patch_kernel(PatchArgs a)
         patch_store(src, s, a.lattice, G, P, a.threads);
 }
 
+// ---------------------------------------------------------------------------
+// Small lattices: one workgroup, one quad per thread (escg_whole.hpp)
+// ---------------------------------------------------------------------------
+
+// L <= 88: at most 484 quads.
+constexpr uint32_t kWholeMaxL = 88;
+constexpr uint32_t kWholeThreads = 512 + 64;
+
+__host__ __device__ inline uint32_t whole_quads(uint32_t L)
+{
+    return (L >> 1) * ((L + 7) >> 3);
+}
+
+// Dynamic LDS: three copies of the lattice and, when S > 7, a histogram.
+// blockDim: the quads' threads (whole waves) and the counting wave.
+template <bool kPacked, bool kProb>
+__global__ __launch_bounds__(kWholeThreads) void whole_kernel(JobDev J,
+                                                              uint8_t *base)
+{
+    extern __shared__ __align__(16) uint8_t smem[];
+    __shared__ LdsTables<kPacked ? 8 : 32> TB;
+    const WholeGeom G = whole_geom(J.L);
+    const uint32_t tid = threadIdx.x, nt = blockDim.x - 64;
+    const uint32_t L = J.L, S = J.S, size = L * G.LS, nw = L * G.Q();
+    const uint32_t k0 = (uint32_t)J.seed, k1 = (uint32_t)(J.seed >> 32);
+    // the state before the MCS, and the two copies its passes write
+    uint8_t *cur = smem, *p1 = smem + size, *p2 = smem + 2 * size;
+    uint32_t *const hist = reinterpret_cast<uint32_t *>(smem + 3 * size);
+    uint8_t *const g = base + J.lat_off;
+    const uint32_t ndw = 3 * size / 4 + (kPacked ? 0u : 32u * kCountSlots);
+    for (uint32_t i = tid; i < ndw; i += blockDim.x)
+        reinterpret_cast<uint32_t *>(smem)[i] = 0;
+    if (tid == 0)
+        TB.misc[0] = 0;
+    __syncthreads();
+    whole_load(cur, g, G);
+    setup_tables(TB, J.dom, J.moore != 0, kProb ? J.ab : nullptr);
+    const auto qc = make_quad_ctx<kProb>(TB, J.T1, J.T2); // after a barrier
+    const auto rotate = [&] { // after an MCS: its state is in p2
+        uint8_t *const x = p2;
+        p2 = p1;
+        p1 = cur;
+        cur = x;
+    };
+
+    if (tid >= nt) { // the counting wave: meets every barrier below
+        const uint32_t lane = tid & 63u, ns = count_states(S);
+        uint32_t n = 0; // the count of species `lane`
+        uint32_t p4[2], p6[3], p8[4];
+        const auto sums = [&](uint32_t stage) {
+            if constexpr (kPacked) {
+                if (stage == 0) {
+                    p4[0] = p4[1] = p6[0] = p6[1] = p6[2] = 0;
+                    p8[0] = p8[1] = p8[2] = p8[3] = 0;
+                }
+                if (ns == 4)
+                    whole_word_sums<4>(cur, nw, stage, p4);
+                else if (ns == 6)
+                    whole_word_sums<6>(cur, nw, stage, p6);
+                else
+                    whole_word_sums<8>(cur, nw, stage, p8);
+            } else {
+                whole_hist(cur, nw, stage, hist);
+            }
+        };
+        // the counts of state t; whether it meets the stop condition
+        const auto close = [&](uint32_t t) {
+            if constexpr (kPacked) {
+                n = ns == 4   ? pair_sums_count<4>(p4, lane, L * L)
+                    : ns == 6 ? pair_sums_count<6>(p6, lane, L * L)
+                              : pair_sums_count<8>(p8, lane, L * L);
+            } else { // one wave's LDS accesses run in order
+                const uint32_t x = patch_hist_sum(hist, lane, size - L * L);
+                n = (uint32_t)__builtin_amdgcn_ds_bpermute(
+                    8 * (int)(lane & 31u), (int)x);
+            }
+            if (J.counts && lane <= S)
+                J.counts[(size_t)t * (S + 1) + lane] = n;
+            if (J.mode == ESCG_STOP_NONE)
+                return false;
+            const uint32_t alive =
+                __popcll(__ballot(lane >= 1 && lane <= S && n > 0));
+            return J.mode == ESCG_STOP_FIRST_EXTINCTION ? alive < S
+                                                        : alive <= 1;
+        };
+        uint32_t t = 0;
+        bool stop = false;
+        for (; t < J.max_mcs; ++t) {
+            sums(0);
+            __syncthreads();
+            sums(1);
+            __syncthreads();
+            sums(2);
+            __syncthreads();
+            stop = close(t);
+            if (stop && lane == 0)
+                TB.misc[0] = 1;
+            __syncthreads();
+            if (stop)
+                break;
+            rotate();
+        }
+        if (!stop) {
+            sums(0);
+            sums(1);
+            sums(2);
+            stop = close(t);
+        }
+        if (J.result) { // lane v holds the count of species v
+            if (lane == 0) {
+                J.result[0] = stop ? 1u : 0u;
+                J.result[1] = t;
+            }
+            if (lane <= S)
+                J.result[2 + lane] = n;
+        }
+        return;
+    }
+
+    PatchList<1> T;
+    const WholeQuad W = whole_quad(G, T);
+    const bool seam = G.part() != 0;
+    Words rf = philox(W.c0, J.mcs0, kTagPass << 8, J.replica, k0, k1);
+    QuadSel sf = quad_sel(rf, qc);
+    uint32_t s = 0, offs = 0; // shift of cur
+    for (uint32_t t = 0; t < J.max_mcs; ++t) {
+        const uint32_t mt = J.mcs0 + t;
+        if ((t & 63u) == 0)
+            offs = patch_offsets(mt, J.replica, k0, k1);
+        const uint32_t off = __builtin_amdgcn_readlane((int)offs, t & 63u);
+#pragma unroll
+        for (uint32_t p = 0; p < 4; ++p) {
+            const uint32_t w = off >> (2 * p);
+            whole_pass(p == 0 ? cur : (p & 1u) ? p1 : p2, (p & 1u) ? p2 : p1,
+                       p == 0 ? s : (off >> (2 * p - 2)) & 1u, G, W, T, seam,
+                       w, p < 3 ? mt : mt + 1,
+                       (kTagPass << 8) | ((p + 1) & 3u), J.replica, k0, k1,
+                       qc, rf, sf);
+            __syncthreads();
+        }
+        if (TB.misc[0]) // the state before this MCS is the result
+            break;
+        rotate();
+        s = (off >> 6) & 1u;
+    }
+    for (uint32_t i = tid; i < nw; i += nt) {
+        const uint32_t r = i / G.Q();
+        whole_store_word(*reinterpret_cast<const uint2 *>(cur + 8 * i), s, r,
+                         i - r * G.Q(), g, G);
+    }
+}
+
 // What a patch launch needs set: exchange slot 0 tagged 0, slot 1 tagged 1
 // (neither matches its first use), the abort words and the count rows 0.
 __global__ void patch_prep_kernel(uint32_t *exch, uint32_t slot_dwords,
@@ -1577,12 +1730,31 @@ const void *persistent_kernel(bool packed, bool prob, bool list)
     return fns[(packed ? 4 : 0) | (prob ? 2 : 0) | (list ? 1 : 0)];
 }
 
+escg_status launch_whole(const JobDev &J, bool small, uint8_t *base,
+                         hipStream_t st);
+
 escg_status launch_lds_single(const JobDev &J, bool small, uint8_t *base,
                               hipStream_t st)
 {
+    if (J.L <= kWholeMaxL)
+        return launch_whole(J, small, base, st);
     const size_t lds = lds_job_bytes(J.L, J.S);
     const uint32_t nt = lds_threads(J.L);
     const void *fn = ESCG_KERNEL2(lds_single_kernel, small, J.ab != nullptr);
+    allow_dynamic_lds(fn, lds);
+    JobDev j = J;
+    void *args[] = {&j, &base};
+    return last_hip(hipLaunchKernel(fn, dim3(1), dim3(nt), args, lds, st));
+}
+
+// A small lattice (L <= kWholeMaxL) with one quad per thread.
+escg_status launch_whole(const JobDev &J, bool small, uint8_t *base,
+                         hipStream_t st)
+{
+    const uint32_t nt = (whole_quads(J.L) + 63) / 64 * 64 + 64;
+    const size_t lds = 3 * lds_job_bytes(J.L, J.S) +
+                       (small ? 0 : 32 * kCountSlots * sizeof(uint32_t));
+    const void *fn = ESCG_KERNEL2(whole_kernel, small, J.ab != nullptr);
     allow_dynamic_lds(fn, lds);
     JobDev j = J;
     void *args[] = {&j, &base};
@@ -2658,7 +2830,7 @@ Route choose_route(const escg_params *p, hipStream_t st, bool until)
         return (L & 7u) == 0 && plan_resident(p).ok();
     };
     const auto ragged_ok = [&] {
-        if (L < kPersistentMinL || (until && fits_lds))
+        if (L <= kWholeMaxL || (until && fits_lds))
             return false;
         hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
         if (hipStreamIsCapturing(st, &cs) != hipSuccess)

@@ -1,0 +1,207 @@
+// escg_whole.hpp -- a small lattice whole in one workgroup's LDS, one quad per
+// thread.
+//
+// What bounds it: latency.  With at most one quad per thread (L <= 88, one to
+// two waves a SIMD) a pass is one chain of row reads, rule lookup, stores and
+// a barrier, whatever the lattice holds.  So, as in the patch kernel
+// (escg_patch.hpp: the two copies of the lattice and their shifts, the row's
+// partial quad and its gap, the counting wave): a pass reads one copy and
+// writes another with aligned stores and one barrier, the next pass's draws
+// and selector lookups run in the shadow of the rows', and a wave of its own
+// counts the species and tests the stop condition while the next MCS runs.
+// Three copies: an MCS's four passes go from the first to the second and then
+// to and fro between the other two, so the state that is being counted, and
+// is the result if it meets the stop condition, outlives them.
+// The lattice wraps inside the copies: the column past a row's last quad is
+// its first one's, the row below the last is row 0.
+#pragma once
+
+#include "escg_patch.hpp"
+
+namespace escg {
+
+struct WholeGeom {
+    uint32_t L, LS; // side, LDS row stride 8 ceil(L / 8)
+    __host__ __device__ uint32_t Q() const { return LS >> 3; }
+    __host__ __device__ uint32_t part() const { return (L >> 1) & 3u; }
+};
+
+__host__ __device__ inline WholeGeom whole_geom(uint32_t L)
+{
+    return WholeGeom{L, (L + 7) & ~7u};
+}
+
+// A thread's quad, fixed for the run; threads past the last quad repeat it.
+struct WholeQuad {
+    uint32_t c0;         // Philox counter word
+    uint32_t pa;         // LDS offset of the top row for oy = 0
+    uint32_t pd;         // of the bottom row for oy = 1 (wrapped)
+    uint32_t left, right; // offsets from a row's word to the dword before it
+                          // and after it (wrapped)
+};
+
+// The quad's list entry for patch_swap as well: its selectors and whether it
+// is the row's partial quad.
+__device__ inline WholeQuad whole_quad(const WholeGeom &G, PatchList<1> &T)
+{
+    const uint32_t Q = G.Q(), Lb = G.L >> 1, nq = Lb * Q;
+    const uint32_t q = min((uint32_t)threadIdx.x, nq - 1u);
+    const uint32_t row = q / Q, col = q - row * Q;
+    WholeQuad W;
+    W.c0 = q;
+    W.pa = 2 * row * G.LS + 8 * col;
+    W.pd = row + 1 == Lb ? 8 * col : W.pa + 2 * G.LS;
+    W.left = col == 0 ? G.LS - 4 : 0u - 4u;
+    W.right = col + 1 == Q ? 8 - G.LS : 8u;
+    patch_swap_selectors(G.part(), T);
+    T.part[0] = G.part() && col + 1 == Q;
+    return W;
+}
+
+// One pass from `src` (shift s) to `dst` (shift ox) with offsets w; (rf, sf),
+// `ctr` and `t`: as patch_pass (one quad per thread), ctr and t being those
+// of the pass that follows.
+template <class Ctx>
+__device__ __forceinline__ void whole_pass(const uint8_t *src, uint8_t *dst,
+                                           uint32_t s, const WholeGeom &G,
+                                           const WholeQuad &W,
+                                           const PatchList<1> &T, bool seam,
+                                           uint32_t w, uint32_t t,
+                                           uint32_t ctr, uint32_t replica,
+                                           uint32_t k0, uint32_t k1,
+                                           const Ctx &qc, Words &rf,
+                                           QuadSel &sf)
+{
+    const uint32_t ox = w & 1u;
+    const bool oy = w & 2u, back = ox < s;
+    const uint32_t pa = W.pa + (oy ? G.LS : 0u);
+    const uint32_t pc = oy ? W.pd : W.pa + G.LS;
+    const uint32_t sh = (ox - s) & 3u, side = back ? W.left : W.right;
+    const uint2 ra = *reinterpret_cast<const uint2 *>(src + pa);
+    const uint2 rc = *reinterpret_cast<const uint2 *>(src + pc);
+    const uint32_t xa = *reinterpret_cast<const uint32_t *>(src + (pa + side));
+    const uint32_t xc = *reinterpret_cast<const uint32_t *>(src + (pc + side));
+    const Words rn = philox(W.c0, t, ctr, replica, k0, k1);
+    const QuadSel qn = quad_sel(rn, qc);
+    // the three dwords the window is cut from: side word first or last
+    const uint32_t d0 = back ? xa : ra.x, d1 = back ? ra.x : ra.y,
+                   d2 = back ? ra.y : xa;
+    const uint32_t e0 = back ? xc : rc.x, e1 = back ? rc.x : rc.y,
+                   e2 = back ? rc.y : xc;
+    uint32_t a0 = __builtin_amdgcn_alignbyte(d1, d0, sh);
+    uint32_t a1 = __builtin_amdgcn_alignbyte(d2, d1, sh);
+    uint32_t c0 = __builtin_amdgcn_alignbyte(e1, e0, sh);
+    uint32_t c1 = __builtin_amdgcn_alignbyte(e2, e1, sh);
+    if (seam && ox) {
+        patch_swap(a0, a1, T, 0);
+        patch_swap(c0, c1, T, 0);
+    }
+    quad_update_sel(a0, a1, c0, c1, rf, sf, qc);
+    if (seam && ox) {
+        patch_swap(a0, a1, T, 0);
+        patch_swap(c0, c1, T, 0);
+    }
+    *reinterpret_cast<uint2 *>(dst + pa) = make_uint2(a0, a1);
+    *reinterpret_cast<uint2 *>(dst + pc) = make_uint2(c0, c1);
+    rf = rn;
+    sf = qn;
+}
+
+// Loads the lattice (shift 0) into `buf`, which holds zeros.
+__device__ inline void whole_load(uint8_t *buf, const uint8_t *g,
+                                  const WholeGeom &G)
+{
+    const uint32_t L = G.L;
+    if ((L & 3u) == 0) {
+        const uint32_t dwr = L >> 2;
+        const uint32_t *g32 = reinterpret_cast<const uint32_t *>(g);
+        for (uint32_t i = threadIdx.x; i < L * dwr; i += blockDim.x)
+            *reinterpret_cast<uint32_t *>(buf + (i / dwr) * G.LS +
+                                          4 * (i % dwr)) = g32[i];
+    } else {
+        const uint32_t hr = L >> 1;
+        const uint16_t *g16 = reinterpret_cast<const uint16_t *>(g);
+        for (uint32_t i = threadIdx.x; i < L * hr; i += blockDim.x)
+            *reinterpret_cast<uint16_t *>(buf + (i / hr) * G.LS +
+                                          2 * (i % hr)) = g16[i];
+    }
+}
+
+// Writes the word (row r, quad j) of a copy of shift s to the lattice.
+__device__ inline void whole_store_word(uint2 v, uint32_t s, uint32_t r,
+                                        uint32_t j, uint8_t *g,
+                                        const WholeGeom &G)
+{
+    const uint32_t Q = G.Q(), part = G.part();
+    const uint32_t cols = part && j + 1 == Q ? 2 * part : 8u;
+    uint8_t *row = g + (size_t)r * G.L;
+#pragma unroll
+    for (uint32_t b = 0; b < 8; ++b) {
+        const uint8_t x = (uint8_t)((b < 4 ? v.x : v.y) >> (8 * (b & 3u)));
+        if (s && b == 7) // the next quad's first column
+            row[j + 1 == Q ? 0u : 8 * j + 8] = x;
+        else if (b + s < cols)
+            row[8 * j + b + s] = x;
+    }
+}
+
+// The counting wave: words lane + 64 k of the lattice, kWholeStage of them a
+// lane in each of three stages.
+constexpr uint32_t kWholeStage = 6;
+
+__device__ __forceinline__ uint2 whole_word(const uint8_t *buf, uint32_t n,
+                                            uint32_t k)
+{
+    const uint32_t i = (threadIdx.x & 63u) + 64 * k;
+    return 64 * k < n && i < n
+               ? *reinterpret_cast<const uint2 *>(buf + 8 * i)
+               : make_uint2(0u, 0u);
+}
+
+// Adds the linear sums of a lane's words of `stage` to `pair` (two 16-bit
+// sums a dword, as patch_word_sums; n words in all; over a wave they stay
+// below 64 * 18 * 8 * 7 < 2^16).
+template <int NS>
+__device__ __forceinline__ void whole_word_sums(const uint8_t *buf, uint32_t n,
+                                                uint32_t stage,
+                                                uint32_t (&pair)[NS / 2])
+{
+    constexpr int NP = (NS - 2) / 2;
+    static_assert(kWholeStage <= 7, "a nibble holds 7 words' counts");
+    uint32_t sv = 0, cp[NP];
+#pragma unroll
+    for (int k = 0; k < NP; ++k)
+        cp[k] = 0;
+#pragma unroll
+    for (uint32_t w = 0; w < kWholeStage; ++w) {
+        const uint2 v = whole_word(buf, n, stage * kWholeStage + w);
+        sv += v.x + v.y;
+#pragma unroll
+        for (int k = 0; k < NP; ++k) {
+            const uint64_t t = pair_code_table(k);
+            const uint32_t hi = (uint32_t)(t >> 32), lo = (uint32_t)t;
+            cp[k] += perm(hi, lo, v.x) + perm(hi, lo, v.y);
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < NP; ++k)
+        pair[k] += __builtin_amdgcn_udot8(cp[k], 0x01010101u, 0u, false) |
+                   __builtin_amdgcn_udot8(cp[k], 0x10101010u, 0u, false) << 16;
+    pair[NP] = __builtin_amdgcn_udot4(sv, 0x01010101u, pair[NP], false);
+}
+
+// Adds a lane's words of `stage` to the histogram (S > 7; gap bytes count as
+// zeros).
+__device__ __forceinline__ void whole_hist(const uint8_t *buf, uint32_t n,
+                                           uint32_t stage, uint32_t *hist)
+{
+    uint32_t *const h = hist + (threadIdx.x & (kCountSlots - 1));
+    for (uint32_t w = 0; w < kWholeStage; ++w) {
+        const uint32_t i =
+            (threadIdx.x & 63u) + 64 * (stage * kWholeStage + w);
+        if (i < n)
+            patch_hist_word(*reinterpret_cast<const uint2 *>(buf + 8 * i), h);
+    }
+}
+
+} // namespace escg

@@ -1,4 +1,5 @@
-"""Host emulation of the patch kernel's phases against the oracle, byte for byte: the device headers compiled for the host
+"""Host emulation of the patch kernel's and the small-lattice kernel's phases
+against the oracle, byte for byte: the device headers compiled for the host
 as in test_kernel_emulation_cpu.py, a workgroup's threads one after another
 (a pass reads one copy of the lattice and writes another)."""
 import os
@@ -10,7 +11,8 @@ from tests.test_kernel_emulation_cpu import (EMU, emu_dir,  # noqa: F401
                                              pytestmark)
 
 
-@pytest.mark.parametrize("prog,expect", [("emu_patch", "patch cases ok")])
+@pytest.mark.parametrize("prog,expect", [("emu_patch", "patch cases ok"),
+                                         ("emu_whole", "whole cases ok")])
 def test_device_logic_matches_oracle(emu_dir, prog, expect):  # noqa: F811
     exe = os.path.join(emu_dir, prog)
     subprocess.check_call(
