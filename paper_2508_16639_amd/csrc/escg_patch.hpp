@@ -137,6 +137,28 @@ __device__ inline void patch_load(uint8_t *buf, const uint8_t *g,
     }
 }
 
+// Stores the first 2 nb columns of a quad's row v to d (rows of side L are
+// 4-byte aligned when L % 4 == 0, where nb is 2 or 4, and 2-byte otherwise).
+__device__ __forceinline__ void store_quad_row(uint8_t *d, uint2 v,
+                                               uint32_t nb, uint32_t L)
+{
+    if ((L & 3u) == 0) {
+        uint32_t *d4 = reinterpret_cast<uint32_t *>(d);
+        d4[0] = v.x;
+        if (nb > 2)
+            d4[1] = v.y;
+    } else {
+        uint16_t *d2 = reinterpret_cast<uint16_t *>(d);
+        d2[0] = (uint16_t)v.x;
+        if (nb > 1)
+            d2[1] = (uint16_t)(v.x >> 16);
+        if (nb > 2)
+            d2[2] = (uint16_t)v.y;
+        if (nb > 3)
+            d2[3] = (uint16_t)(v.y >> 16);
+    }
+}
+
 // Stores the interior columns from the copy `buf` of shift s: column 8 j of
 // the region is byte 8 j - s (the column before a quad's first byte is the
 // last byte of the quad before it, the partial one included).
@@ -157,29 +179,14 @@ __device__ inline void patch_store(const uint8_t *buf, uint32_t s, uint8_t *g,
             v.y = __builtin_amdgcn_alignbyte(v.y, v.x, 3);
             v.x = (v.x << 8) | y;
         }
-        uint8_t *d = g + (size_t)(2 * P.b0 + r) * L + 8 * q;
-        if ((L & 3u) == 0) {
-            uint32_t *d4 = reinterpret_cast<uint32_t *>(d);
-            d4[0] = v.x;
-            if (nb > 2)
-                d4[1] = v.y;
-        } else {
-            uint16_t *d2 = reinterpret_cast<uint16_t *>(d);
-            d2[0] = (uint16_t)v.x;
-            if (nb > 1)
-                d2[1] = (uint16_t)(v.x >> 16);
-            if (nb > 2)
-                d2[2] = (uint16_t)v.y;
-            if (nb > 3)
-                d2[3] = (uint16_t)(v.y >> 16);
-        }
+        store_quad_row(g + (size_t)(2 * P.b0 + r) * L + 8 * q, v, nb, L);
     }
 }
 
 // A thread's quads, fixed for the run: quad tid + i * threads in row-major
 // order over (region block row, quad column), i < kSlots.  Lanes past the
 // last quad repeat it (they store the same bytes), so that a pass needs no
-// lane masks; a wave with no quad at all in slot i > 0 skips it.  A pass with
+// lane masks; a wave with no quad in the last slot skips it.  A pass with
 // row offset 1 updates the last block row too, with the spare row below the
 // region: both rows are stale then in any case.
 template <int kSlots>
@@ -290,67 +297,91 @@ __device__ __forceinline__ void patch_pass(const uint8_t *src, uint8_t *dst,
     sf = qn;
 }
 
+// The window of a quad whose aligned word is at `pa` (top row) and `pc`, from
+// a copy of shift kSrcOdd, for a pass with column offset kOdd: aligned, or one
+// byte to the right or left of the aligned word; right / left: offsets to the
+// byte after and to the dword before the word.
+template <bool kOdd, bool kSrcOdd>
+__device__ __forceinline__ QuadRows load_window(const uint8_t *src,
+                                                uint32_t pa, uint32_t pc,
+                                                int32_t left = -4,
+                                                int32_t right = 8)
+{
+    const uint2 ra = *reinterpret_cast<const uint2 *>(src + pa);
+    const uint2 rc = *reinterpret_cast<const uint2 *>(src + pc);
+    if (kOdd == kSrcOdd)
+        return QuadRows{ra.x, ra.y, rc.x, rc.y};
+    if (kOdd) {
+        const uint32_t xa = src[(int32_t)pa + right],
+                       xc = src[(int32_t)pc + right];
+        return QuadRows{__builtin_amdgcn_alignbyte(ra.y, ra.x, 1),
+                        __builtin_amdgcn_alignbyte(xa, ra.y, 1),
+                        __builtin_amdgcn_alignbyte(rc.y, rc.x, 1),
+                        __builtin_amdgcn_alignbyte(xc, rc.y, 1)};
+    }
+    const uint32_t xa =
+        *reinterpret_cast<const uint32_t *>(src + ((int32_t)pa + left));
+    const uint32_t xc =
+        *reinterpret_cast<const uint32_t *>(src + ((int32_t)pc + left));
+    return QuadRows{__builtin_amdgcn_alignbyte(ra.x, xa, 3),
+                    __builtin_amdgcn_alignbyte(ra.y, ra.x, 3),
+                    __builtin_amdgcn_alignbyte(rc.x, xc, 3),
+                    __builtin_amdgcn_alignbyte(rc.y, rc.x, 3)};
+}
+
 // Several quads per thread: the pass for one (ox, s), which needs fewer LDS
-// reads and no byte shift when ox = s; dy: oy * LS.  The Philox words and
-// selector pairs of slot i + 1 are computed before slot i is updated.
+// reads and no byte shift when ox = s; dy: oy * LS.  Every wave runs the
+// first kSlots - 1 slots (a wave with fewer repeats its last quad), so that
+// they are straight-line code, each slot's draws made before the slot before
+// it is updated and the next pass's first ones before the last of them; the
+// last slot is one block of its own for the waves that fill it.  (With a test
+// per slot the draws handed from slot to slot cost 13 v_mov of 76
+// instructions a quad, 3 % of the time at L = 3200.)
 template <bool kOdd, bool kSrcOdd, bool kSeam, int kSlots, class Ctx>
 __device__ __forceinline__ void patch_pass_slots(
     const uint8_t *src, uint8_t *dst, uint32_t LS, uint32_t dy,
     const PatchList<kSlots> &T, PassIndex ix, PassIndex nx, uint32_t replica,
     uint32_t k0, uint32_t k1, const Ctx &qc, Words &rf, QuadSel &sf)
 {
-    Words r = rf;
-    QuadSel qs = sf;
-#pragma unroll
-    for (uint32_t i = 0; i < (uint32_t)kSlots; ++i) {
-        if (i > 0 && i >= T.n)
-            break;
+    const auto draw = [&](uint32_t i, PassIndex at) {
+        return philox(T.c0[i], at.t, (kTagPass << 8) | at.p, replica, k0, k1);
+    };
+    const auto update = [&](uint32_t i, QuadRows &q, const Words &r,
+                            const QuadSel &qs) {
+        if (kOdd && kSeam) {
+            patch_swap(q.a0, q.a1, T, i);
+            patch_swap(q.c0, q.c1, T, i);
+        }
+        quad_update_sel(q.a0, q.a1, q.c0, q.c1, r, qs, qc);
+        if (kOdd && kSeam) {
+            patch_swap(q.a0, q.a1, T, i);
+            patch_swap(q.c0, q.c1, T, i);
+        }
         const uint32_t pa = T.pa[i] + dy;
-        const uint2 ra = *reinterpret_cast<const uint2 *>(src + pa);
-        const uint2 rc = *reinterpret_cast<const uint2 *>(src + pa + LS);
-        uint32_t xa = 0, xc = 0; // the column past the aligned word
-        if (kOdd && !kSrcOdd) {
-            xa = src[pa + 8];
-            xc = src[pa + LS + 8];
-        } else if (!kOdd && kSrcOdd) { // before it (its dword's byte 3)
-            xa = *reinterpret_cast<const uint32_t *>(src + pa - 4);
-            xc = *reinterpret_cast<const uint32_t *>(src + pa + LS - 4);
-        }
-        Words rn;
-        QuadSel qn;
-        if (i + 1 < (uint32_t)kSlots && i + 1 < T.n) {
-            rn = philox(T.c0[i + 1], ix.t, (kTagPass << 8) | ix.p, replica,
-                        k0, k1);
-            qn = quad_sel(rn, qc);
-        }
-        uint32_t a0 = ra.x, a1 = ra.y, c0 = rc.x, c1 = rc.y;
-        if (kOdd && !kSrcOdd) {
-            a0 = __builtin_amdgcn_alignbyte(ra.y, ra.x, 1);
-            a1 = __builtin_amdgcn_alignbyte(xa, ra.y, 1);
-            c0 = __builtin_amdgcn_alignbyte(rc.y, rc.x, 1);
-            c1 = __builtin_amdgcn_alignbyte(xc, rc.y, 1);
-        } else if (!kOdd && kSrcOdd) {
-            a0 = __builtin_amdgcn_alignbyte(ra.x, xa, 3);
-            a1 = __builtin_amdgcn_alignbyte(ra.y, ra.x, 3);
-            c0 = __builtin_amdgcn_alignbyte(rc.x, xc, 3);
-            c1 = __builtin_amdgcn_alignbyte(rc.y, rc.x, 3);
-        }
-        if (kOdd && kSeam) {
-            patch_swap(a0, a1, T, i);
-            patch_swap(c0, c1, T, i);
-        }
-        quad_update_sel(a0, a1, c0, c1, r, qs, qc);
-        if (kOdd && kSeam) {
-            patch_swap(a0, a1, T, i);
-            patch_swap(c0, c1, T, i);
-        }
-        *reinterpret_cast<uint2 *>(dst + pa) = make_uint2(a0, a1);
-        *reinterpret_cast<uint2 *>(dst + pa + LS) = make_uint2(c0, c1);
-        r = rn;
-        qs = qn;
+        *reinterpret_cast<uint2 *>(dst + pa) = make_uint2(q.a0, q.a1);
+        *reinterpret_cast<uint2 *>(dst + pa + LS) = make_uint2(q.c0, q.c1);
+    };
+    Words r[kSlots];
+    QuadSel qs[kSlots];
+    r[0] = rf;
+    qs[0] = sf;
+#pragma unroll
+    for (uint32_t i = 0; i + 1 < (uint32_t)kSlots; ++i) {
+        const uint32_t pa = T.pa[i] + dy;
+        QuadRows q = load_window<kOdd, kSrcOdd>(src, pa, pa + LS);
+        const bool last = i + 2 == (uint32_t)kSlots;
+        r[i + 1] = last ? draw(0, nx) : draw(i + 1, ix);
+        qs[i + 1] = quad_sel(r[i + 1], qc);
+        update(i, q, r[i], qs[i]);
     }
-    rf = philox(T.c0[0], nx.t, (kTagPass << 8) | nx.p, replica, k0, k1);
-    sf = quad_sel(rf, qc);
+    if (T.n == (uint32_t)kSlots) {
+        const uint32_t i = kSlots - 1, pa = T.pa[i] + dy;
+        QuadRows q = load_window<kOdd, kSrcOdd>(src, pa, pa + LS);
+        const Words w = draw(i, ix);
+        update(i, q, w, quad_sel(w, qc));
+    }
+    rf = r[kSlots - 1];
+    sf = qs[kSlots - 1];
 }
 
 template <bool kSeam, int kSlots, class Ctx>
