@@ -1140,9 +1140,210 @@ __global__ __launch_bounds__(kWholeThreads) void whole_kernel(JobDev J,
     }
     for (uint32_t i = tid; i < nw; i += nt) {
         const uint32_t r = i / G.Q();
-        whole_store_word(*reinterpret_cast<const uint2 *>(cur + 8 * i), s, r,
-                         i - r * G.Q(), g, G);
+        whole_store_word(cur, s, r, i - r * G.Q(), g, G);
     }
+}
+
+// ---------------------------------------------------------------------------
+// Lattices of which a CU's LDS holds two copies (L <= 276 for S <= 7), one
+// 1024-thread workgroup per job and CU, several quads a thread
+// ---------------------------------------------------------------------------
+// Bound by vector issue and, below some 1000 quads, by the four barriers of
+// an MCS.  Against two 512-thread workgroups a CU that update one copy in
+// place (lds_batch_kernel), 512 jobs on 256 CUs, us per MCS and job: L = 256
+// 12.3 -> 10.5, L = 250 16.2 -> 11.3, L = 192 7.7 -> 6.2, L = 128 4.7 -> 3.7,
+// but L = 96 2.7 -> 3.2 and L = 64 1.65 -> 2.6, where the other kernel keeps
+// more jobs on a CU; a job alone on its CU: L = 256 16.0 -> 10.0, L = 64
+// 3.2 -> 2.5.
+constexpr uint32_t kPairThreads = 1024;
+
+// MCS between two tests of the stop condition.  A species that is extinct
+// stays extinct, so a condition that holds at a test has held since some MCS
+// after the last test: the job goes back to the state of that test (kept in
+// its lattice's place in global memory) and tests after every MCS.  Counting
+// after every MCS took a tenth of the instructions.
+constexpr uint32_t kPairCheck = 32;
+
+template <bool kPacked, bool kProb>
+__device__ __forceinline__ void run_job_pair(const JobDev &J, uint8_t *base, uint8_t *smem,
+                             LdsTables<kPacked ? 8 : 32> &TB)
+{
+    const WholeGeom G = whole_geom(J.L);
+    const uint32_t tid = threadIdx.x, nt = blockDim.x;
+    const uint32_t L = J.L, S = J.S, size = L * G.LS, nw = L * G.Q();
+    const uint32_t k0 = (uint32_t)J.seed, k1 = (uint32_t)(J.seed >> 32);
+    uint8_t *src = smem, *dst = smem + size;
+    uint8_t *const g = base + J.lat_off;
+    uint32_t s = 0, t = 0, step = kPairCheck; // s: shift of src
+
+    const auto zero = [&] {
+        for (uint32_t i = tid; i < size / 8; i += nt)
+            reinterpret_cast<uint2 *>(src)[i] = make_uint2(0u, 0u);
+        __syncthreads();
+    };
+    const auto store = [&] {
+        for (uint32_t i = tid; i < nw; i += nt) {
+            const uint32_t r = i / G.Q();
+            whole_store_word(src, s, r, i - r * G.Q(), g, G);
+        }
+    };
+    zero();
+    if (J.init) {
+        for (uint32_t i = tid; i < (L * L) >> 2; i += nt) {
+            const Words w = philox(i, 0u, kTagInit << 8, J.replica, k0, k1);
+#pragma unroll
+            for (uint32_t j = 0; j < 4; ++j) {
+                const uint32_t n = 4u * i + j, r = n / L;
+                src[r * G.LS + (n - r * L)] =
+                    (uint8_t)(((uint64_t)pick(w, j) * (S + 1u)) >> 32);
+            }
+        }
+    } else {
+        whole_load(src, g, G);
+    }
+    setup_tables(TB, J.dom, J.moore != 0, kProb ? J.ab : nullptr);
+    const auto qc = make_quad_ctx<kProb>(TB, J.T1, J.T2); // after a barrier
+
+    // counts of the state in src: S <= 7 into c[] (uniform), else into
+    // TB.cnt[0..S]; returns the stop test (TB.cnt: slots, cleared by
+    // setup_tables, or the counts)
+    uint32_t c[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+    uint32_t prev[7] = {0, 0, 0, 0, 0, 0, 0};
+    const uint32_t ns = count_states(S);
+    const auto test = [&] {
+        const uint32_t *src32 = reinterpret_cast<const uint32_t *>(src);
+        if constexpr (kPacked) {
+            if (ns == 4) {
+                lds_count_sums<4>(src32, size / 4, TB.cnt);
+                __syncthreads();
+                lds_count_close<4>(TB.cnt, prev, L * L, 0, c);
+            } else if (ns == 6) {
+                lds_count_sums<6>(src32, size / 4, TB.cnt);
+                __syncthreads();
+                lds_count_close<6>(TB.cnt, prev, L * L, 0, c);
+            } else {
+                lds_count_sums<8>(src32, size / 4, TB.cnt);
+                __syncthreads();
+                lds_count_close<8>(TB.cnt, prev, L * L, 0, c);
+            }
+            __syncthreads();
+            return stop_met8(c, S, J.mode);
+        } else {
+            if (tid < 32) // gap bytes count as zeros
+                TB.cnt[tid] = tid == 0 ? L * L - size : 0u;
+            __syncthreads();
+            count_dwords_wide(src32, size / 4, S, TB.cnt);
+            __syncthreads();
+            const bool met = stop_met(TB.cnt, S, J.mode);
+            __syncthreads();
+            return met;
+        }
+    };
+    // n <= 64 MCS (a call would keep the lattice's state in scratch memory)
+    const auto advance = [&](uint32_t n, auto slots)
+        __attribute__((always_inline)) {
+        constexpr int kSlots = decltype(slots)::value;
+        WholeSlots<kSlots> W = whole_slots<kSlots>(G, nt);
+        const uint32_t t0 = J.mcs0 + t, replica = J.replica;
+        const uint32_t offs = patch_offsets(t0, replica, k0, k1);
+        Words rf = philox(W.c0[0], t0, kTagPass << 8, replica, k0, k1);
+        QuadSel sf = quad_sel(rf, qc);
+#pragma unroll 1
+        for (uint32_t m = 0; m < n; ++m) {
+            const uint32_t off = __builtin_amdgcn_readlane((int)offs, m);
+#pragma unroll 2
+            for (uint32_t p = 0; p < 4; ++p) {
+                const uint32_t w = off >> (2 * p);
+                whole_pass_slots<kSlots>(
+                    src, dst, s, G, W, w, PassIndex{t0 + m, p},
+                    p < 3 ? PassIndex{t0 + m, p + 1}
+                          : PassIndex{t0 + m + 1, 0u},
+                    replica, k0, k1, qc, rf, sf);
+                uint8_t *const x = src;
+                src = dst;
+                dst = x;
+                s = w & 1u;
+                __syncthreads();
+            }
+        }
+    };
+    const uint32_t slots = ((L >> 1) * G.Q() + nt - 1) / nt;
+    bool stop = test();
+    if (J.init && J.mode != ESCG_STOP_NONE && !stop && J.max_mcs > 0)
+        store();
+    while (!stop && t < J.max_mcs) {
+        const uint32_t n = J.mode == ESCG_STOP_NONE
+                               ? min(64u, J.max_mcs - t)
+                               : min(step, J.max_mcs - t);
+        switch (slots) {
+        case 1: advance(n, std::integral_constant<int, 1>()); break;
+        case 2: advance(n, std::integral_constant<int, 2>()); break;
+        case 3: advance(n, std::integral_constant<int, 3>()); break;
+        case 4: advance(n, std::integral_constant<int, 4>()); break;
+        default: advance(n, std::integral_constant<int, 5>()); break;
+        }
+        t += n;
+        if (J.mode == ESCG_STOP_NONE) {
+            if (t == J.max_mcs)
+                (void)test(); // the counts
+            continue;
+        }
+        stop = test();
+        if (stop && n > 1) { // back to the last test, one MCS at a time
+            t -= n;
+            step = 1;
+            stop = false;
+            __threadfence(); // the stores of that state, by all threads
+            zero();
+            whole_load(src, g, G);
+            s = 0;
+            __syncthreads();
+        } else if (!stop && step > 1 && t < J.max_mcs) {
+            store();
+        }
+    }
+    store();
+    if (J.result) {
+        for (uint32_t i = tid; i < J.result_words; i += nt) {
+            uint32_t v = 0;
+            if (i == 0)
+                v = stop ? 1u : 0u;
+            else if (i == 1)
+                v = t;
+            else if (i - 2 <= S)
+                v = kPacked ? pick8(c, i - 2) : TB.cnt[i - 2];
+            J.result[i] = v;
+        }
+    }
+    __syncthreads();
+}
+
+template <bool kPacked, bool kProb>
+__global__ __launch_bounds__(kPairThreads) void pair_batch_kernel(
+    const JobDev *__restrict__ jobs, const uint32_t *__restrict__ order,
+    uint32_t n, uint32_t *queue, uint8_t *base)
+{
+    extern __shared__ __align__(16) uint8_t smem[];
+    __shared__ LdsTables<kPacked ? 8 : 32> TB;
+    for (;;) {
+        if (threadIdx.x == 0)
+            TB.misc[0] = atomicAdd(queue, 1u);
+        __syncthreads();
+        const uint32_t qi = TB.misc[0];
+        __syncthreads();
+        if (qi >= n)
+            return;
+        run_job_pair<kPacked, kProb>(jobs[order[qi]], base, smem, TB);
+    }
+}
+
+template <bool kPacked, bool kProb>
+__global__ __launch_bounds__(kPairThreads) void pair_single_kernel(
+    JobDev J, uint8_t *base)
+{
+    extern __shared__ __align__(16) uint8_t smem[];
+    __shared__ LdsTables<kPacked ? 8 : 32> TB;
+    run_job_pair<kPacked, kProb>(J, base, smem, TB);
 }
 
 // What a patch launch needs set: exchange slot 0 tagged 0, slot 1 tagged 1
@@ -1733,14 +1934,28 @@ const void *persistent_kernel(bool packed, bool prob, bool list)
 escg_status launch_whole(const JobDev &J, bool small, uint8_t *base,
                          hipStream_t st);
 
+// Two copies of a lattice of lds_job_bytes `bytes` beside the tables of S.
+bool pair_fits(size_t bytes, uint32_t S)
+{
+    const DeviceInfo di = device_info();
+    return 2 * bytes + static_lds_bytes(S) + 64 <=
+           (di.lds_max ? di.lds_max : 65536);
+}
+
 escg_status launch_lds_single(const JobDev &J, bool small, uint8_t *base,
                               hipStream_t st)
 {
     if (J.L <= kWholeMaxL)
         return launch_whole(J, small, base, st);
-    const size_t lds = lds_job_bytes(J.L, J.S);
-    const uint32_t nt = lds_threads(J.L);
-    const void *fn = ESCG_KERNEL2(lds_single_kernel, small, J.ab != nullptr);
+    // without count rows the counts of a test every 32 MCS do (L = 100:
+    // 9.9 -> 2.6 us per MCS, L = 250: 33 -> 11)
+    const bool pair =
+        !J.counts && pair_fits(lds_job_bytes(J.L, J.S), J.S);
+    const size_t lds = (pair ? 2 : 1) * lds_job_bytes(J.L, J.S);
+    const uint32_t nt = pair ? kPairThreads : lds_threads(J.L);
+    const void *fn =
+        pair ? ESCG_KERNEL2(pair_single_kernel, small, J.ab != nullptr)
+             : ESCG_KERNEL2(lds_single_kernel, small, J.ab != nullptr);
     allow_dynamic_lds(fn, lds);
     JobDev j = J;
     void *args[] = {&j, &base};
@@ -3531,10 +3746,30 @@ escg_status escg_batch_run(uint32_t n, const escg_params *h_params,
     // capped at the kernel's 512, resident workgroups per CU capped at what
     // fits)
     const escg_launch &ln = h_params[0].launch;
-    const size_t lds = lds_need;
-    const uint32_t nt = ln.threads ? std::min(ln.threads, 512u)
-                                   : lds_threads(Lmax);
-    const void *fn = ESCG_KERNEL2(lds_batch_kernel, all_small, prob);
+    // two copies of a lattice and 1024 threads, or one copy and several
+    // workgroups per CU: the first where every job can have a CU of its own
+    // (or the caller allows no more workgroups), else whichever the measured
+    // us per MCS and job (see run_job_pair; q quads, other sides of
+    // L % 8 != 0 a third slower in place) say
+    const uint32_t cus = (uint32_t)std::max(1, device_info().cus);
+    bool pair = !ln.threads && !ln.wg_per_cu &&
+                pair_fits(lds_need, all_small ? 7u : ESCG_MAX_SPECIES);
+    if (pair && n > cus && (ln.max_wgs == 0 || ln.max_wgs > cus)) {
+        double in_place = 0, two_copies = 0;
+        for (uint32_t j = 0; j < n; ++j) {
+            const double q = (double)whole_quads(jobs[j].L);
+            const double m = (double)jobs[j].max_mcs;
+            in_place += m * (1.0 + 2.8e-3 * q) * (jobs[j].L & 7u ? 1.35 : 1.0);
+            two_copies += m * (2.2 + 1.8e-3 * q);
+        }
+        pair = two_copies < in_place;
+    }
+    const size_t lds = pair ? 2 * lds_need : lds_need;
+    const uint32_t nt = pair         ? kPairThreads
+                        : ln.threads ? std::min(ln.threads, 512u)
+                                     : lds_threads(Lmax);
+    const void *fn = pair ? ESCG_KERNEL2(pair_batch_kernel, all_small, prob)
+                          : ESCG_KERNEL2(lds_batch_kernel, all_small, prob);
     allow_dynamic_lds(fn, lds);
     int per_cu = 0;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, nt, lds) !=
@@ -3543,9 +3778,7 @@ escg_status escg_batch_run(uint32_t n, const escg_params *h_params,
         per_cu = 1;
     if (ln.wg_per_cu)
         per_cu = std::min(per_cu, (int)ln.wg_per_cu);
-    const DeviceInfo di = device_info();
-    uint32_t grid =
-        std::min<uint32_t>(n, (uint32_t)std::max(1, di.cus) * per_cu);
+    uint32_t grid = std::min<uint32_t>(n, cus * (uint32_t)per_cu);
     if (ln.max_wgs)
         grid = std::min(grid, ln.max_wgs);
     const JobDev *aj = d_jobs;

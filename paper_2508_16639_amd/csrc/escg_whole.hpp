@@ -107,6 +107,122 @@ __device__ __forceinline__ void whole_pass(const uint8_t *src, uint8_t *dst,
     sf = qn;
 }
 
+// Several quads a thread (larger lattices, two copies): quad tid + i *
+// threads in row-major order, i < kSlots = ceil(quads / threads).  Threads
+// past the last quad repeat it; a wave with no quad in the last slot skips it.
+constexpr uint32_t kWholeSlots = 5;
+
+template <int kSlots>
+struct WholeSlots {
+    bool full;            // the wave has quads in the last slot (uniform)
+    uint32_t pa[kSlots];  // LDS offset of the top row for oy = 0
+    uint32_t pd[kSlots];  // of the bottom row for oy = 1 (wrapped)
+    uint32_t side[kSlots]; // offsets to the dwords before (low half) and
+                           // after (high half) a row's word, wrapped
+    uint32_t c0[kSlots];  // Philox counter word
+    PatchList<1> swap;    // selectors of the partial quad
+};
+
+template <int kSlots>
+__device__ inline WholeSlots<kSlots> whole_slots(const WholeGeom &G,
+                                                 uint32_t threads)
+{
+    const uint32_t Q = G.Q(), Lb = G.L >> 1, nq = Lb * Q;
+    WholeSlots<kSlots> W;
+    W.full = (threadIdx.x & ~63u) + (kSlots - 1) * threads < nq;
+#pragma unroll
+    for (uint32_t i = 0; i < (uint32_t)kSlots; ++i) {
+        const uint32_t q = min(threadIdx.x + i * threads, nq - 1u);
+        const uint32_t row = q / Q, col = q - row * Q;
+        W.pa[i] = 2 * row * G.LS + 8 * col;
+        W.pd[i] = row + 1 == Lb ? 8 * col : W.pa[i] + 2 * G.LS;
+        const uint32_t left = col == 0 ? G.LS - 4 : 0u - 4u;
+        const uint32_t right = col + 1 == Q ? 8 - G.LS : 8u;
+        W.side[i] = (left & 0xFFFFu) | right << 16;
+        W.c0[i] = q;
+    }
+    patch_swap_selectors(G.part(), W.swap);
+    return W;
+}
+
+// One pass from `src` (shift kSrcOdd) to `dst` (shift kOdd), slot by slot as
+// patch_pass_slots.
+template <bool kOdd, bool kSrcOdd, int kSlots, class Ctx>
+__device__ __forceinline__ void whole_pass_slots(
+    const uint8_t *src, uint8_t *dst, const WholeGeom &G,
+    WholeSlots<kSlots> &W, bool oy, PassIndex ix, PassIndex nx,
+    uint32_t replica, uint32_t k0, uint32_t k1, const Ctx &qc, Words &rf,
+    QuadSel &sf)
+{
+    const bool seam = kOdd && G.part() != 0;
+    const auto draw = [&](uint32_t i, PassIndex at) {
+        return philox(W.c0[i], at.t, (kTagPass << 8) | at.p, replica, k0, k1);
+    };
+    const auto top = [&](uint32_t i) { return W.pa[i] + (oy ? G.LS : 0u); };
+    const auto bottom = [&](uint32_t i) {
+        return oy ? W.pd[i] : W.pa[i] + G.LS;
+    };
+    const auto load = [&](uint32_t i) {
+        return load_window<kOdd, kSrcOdd>(src, top(i), bottom(i),
+                                          (int16_t)W.side[i],
+                                          (int32_t)W.side[i] >> 16);
+    };
+    const auto update = [&](uint32_t i, QuadRows &q, const Words &r,
+                            const QuadSel &qs) {
+        if (seam) {
+            W.swap.part[0] = (int32_t)W.side[i] >> 16 != 8;
+            patch_swap(q.a0, q.a1, W.swap, 0);
+            patch_swap(q.c0, q.c1, W.swap, 0);
+        }
+        quad_update_sel(q.a0, q.a1, q.c0, q.c1, r, qs, qc);
+        if (seam) {
+            patch_swap(q.a0, q.a1, W.swap, 0);
+            patch_swap(q.c0, q.c1, W.swap, 0);
+        }
+        *reinterpret_cast<uint2 *>(dst + top(i)) = make_uint2(q.a0, q.a1);
+        *reinterpret_cast<uint2 *>(dst + bottom(i)) = make_uint2(q.c0, q.c1);
+    };
+    Words r[kSlots + 1];
+    QuadSel qs[kSlots + 1];
+    r[0] = rf;
+    qs[0] = sf;
+    constexpr uint32_t n = kSlots == 1 ? 1 : kSlots - 1; // common slots
+#pragma unroll
+    for (uint32_t i = 0; i < n; ++i) {
+        QuadRows q = load(i);
+        r[i + 1] = i + 1 == n ? draw(0, nx) : draw(i + 1, ix);
+        qs[i + 1] = quad_sel(r[i + 1], qc);
+        if (kSlots > 1 || W.full)
+            update(i, q, r[i], qs[i]);
+    }
+    if (kSlots > 1 && W.full) {
+        QuadRows q = load(kSlots - 1);
+        const Words w = draw(kSlots - 1, ix);
+        update(kSlots - 1, q, w, quad_sel(w, qc));
+    }
+    rf = r[n];
+    sf = qs[n];
+}
+
+// The pass with offsets w from (src, shift s).
+template <int kSlots, class Ctx>
+__device__ __forceinline__ void whole_pass_slots(
+    const uint8_t *src, uint8_t *dst, uint32_t s, const WholeGeom &G,
+    WholeSlots<kSlots> &W, uint32_t w, PassIndex ix, PassIndex nx,
+    uint32_t replica, uint32_t k0, uint32_t k1, const Ctx &qc, Words &rf,
+    QuadSel &sf)
+{
+    const bool oy = w & 2u;
+#define ESCG_PASS(O, S)                                                       \
+    whole_pass_slots<O, S, kSlots>(src, dst, G, W, oy, ix, nx, replica, k0,   \
+                                   k1, qc, rf, sf)
+    if (w & 1u)
+        s ? ESCG_PASS(true, true) : ESCG_PASS(true, false);
+    else
+        s ? ESCG_PASS(false, true) : ESCG_PASS(false, false);
+#undef ESCG_PASS
+}
+
 // Loads the lattice (shift 0) into `buf`, which holds zeros.
 __device__ inline void whole_load(uint8_t *buf, const uint8_t *g,
                                   const WholeGeom &G)
@@ -127,22 +243,23 @@ __device__ inline void whole_load(uint8_t *buf, const uint8_t *g,
     }
 }
 
-// Writes the word (row r, quad j) of a copy of shift s to the lattice.
-__device__ inline void whole_store_word(uint2 v, uint32_t s, uint32_t r,
-                                        uint32_t j, uint8_t *g,
-                                        const WholeGeom &G)
+// Writes the columns of quad j, row r of a copy `buf` of shift s to the
+// lattice: with shift 1 the word is one column ahead, so its first column is
+// the last byte of the word before (of the row's last word for j = 0).
+__device__ __forceinline__ void whole_store_word(const uint8_t *buf,
+                                                 uint32_t s, uint32_t r,
+                                                 uint32_t j, uint8_t *g,
+                                                 const WholeGeom &G)
 {
-    const uint32_t Q = G.Q(), part = G.part();
-    const uint32_t cols = part && j + 1 == Q ? 2 * part : 8u;
-    uint8_t *row = g + (size_t)r * G.L;
-#pragma unroll
-    for (uint32_t b = 0; b < 8; ++b) {
-        const uint8_t x = (uint8_t)((b < 4 ? v.x : v.y) >> (8 * (b & 3u)));
-        if (s && b == 7) // the next quad's first column
-            row[j + 1 == Q ? 0u : 8 * j + 8] = x;
-        else if (b + s < cols)
-            row[8 * j + b + s] = x;
+    const uint8_t *row = buf + r * G.LS;
+    uint2 v = *reinterpret_cast<const uint2 *>(row + 8 * j);
+    if (s) {
+        const uint32_t y = row[j == 0 ? G.LS - 1 : 8 * j - 1];
+        v.y = __builtin_amdgcn_alignbyte(v.y, v.x, 3);
+        v.x = (v.x << 8) | y;
     }
+    const uint32_t nb = G.part() && j + 1 == G.Q() ? G.part() : 4u;
+    store_quad_row(g + (size_t)r * G.L + 8 * j, v, nb, G.L);
 }
 
 // The counting wave: words lane + 64 k of the lattice, kWholeStage of them a

@@ -79,7 +79,7 @@ static int run_case(uint32_t L, uint32_t S, bool moore, const double *r) {
     count(t + 1);
   }
   std::vector<uint8_t> out(L * L, 0xEE), ref = g;
-  for (uint32_t i = 0; i < nw; ++i) whole_store_word(*reinterpret_cast<const uint2 *>(cur + 8 * i), s, i / G.Q(), i % G.Q(), out.data(), G);
+  for (uint32_t i = 0; i < nw; ++i) whole_store_word(cur, s, i / G.Q(), i % G.Q(), out.data(), G);
   orc_o2_run(L, S, D.data(), r[0], r[1], r[2], seed, rep, kPhiloxRounds, moore ? 8 : 4, nullptr, mcs0, n, ref.data(), rc.data());
   if (out != ref) { bad++; printf("MISMATCH L=%u S=%u\n", L, S); }
   if (cnt != rc) { bad++; printf("COUNT MISMATCH L=%u S=%u\n", L, S); }
