@@ -69,7 +69,9 @@ typedef int32_t escg_status;
 #define ESCG_STOP_NONE             2u /* run the full MCS budget              */
 
 /* Kernel paths of a single job (escg_launch.route, escg_last_route): the
- * whole lattice in one workgroup's LDS; one tiled launch per MCS; the
+ * whole lattice in one workgroup's LDS; tiled launches (of up to three MCS
+ * each where the library decides, of one where the caller names the route, a
+ * tile shape or a workgroup size); the
  * persistent kernels (all MCS in one cooperative launch, every part of the
  * lattice resident in LDS: uneven patches with deep halos, or equal tiles
  * where the launch choices name a tile shape or a workgroup size, or the
@@ -91,8 +93,8 @@ typedef int32_t escg_status;
  *             (not under stream capture, and not in a run until extinction
  *             that one workgroup's LDS can hold), while the lattice fits
  *             the LDS of all compute units; else the
- *             whole lattice in one workgroup's LDS if it fits, else one
- *             tiled launch per MCS.
+ *             whole lattice in one workgroup's LDS if it fits, else tiled
+ *             launches.
  *   tile_h, tile_w   tile shape of the tiled paths (both 0: the planner's
  *             cost model); must divide L with tile_w % 8 == 0, tile_h even
  *             >= 4 (EINVAL otherwise); a shape whose tile does not fit the
@@ -220,12 +222,12 @@ escg_status escg_step_mcs(const escg_params *p, uint8_t *d_lattice,
  * computation as escg_step_mcs, with the same arguments, results (byte for
  * byte), routing and launch choices, but the call allocates nothing.  Every
  * scratch buffer it needs (the persistent kernel's exchange area and abort
- * word, the per-MCS path's ping-pong lattice, the selection thresholds of
+ * word, the tiled path's ping-pong lattice, the selection thresholds of
  * dominance probabilities) is carved from one file-scope device array of
  * ESCG_STATIC_SCRATCH_BYTES bytes per GPU, which the library holds until the
  * process ends.  A call that would need more returns ESCG_ENOMEM with
  * nothing enqueued and escg_last_error() giving the bytes needed (the
- * per-MCS tiled path takes L*L bytes, the persistent path max(exchange
+ * tiled path takes L*L bytes, the persistent path max(exchange
  * area, L*L), dominance probabilities 8 KiB more: every L <= 8184 fits).  Calls on one GPU share its
  * array and each call initialises what it uses, so calls whose work
  * overlaps on the device (different streams, or different host threads)

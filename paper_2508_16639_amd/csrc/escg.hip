@@ -776,6 +776,13 @@ __device__ __forceinline__ void patch_exchange(const PatchArgs &a,
     }
 }
 
+// Most quads a thread in a pass of the patch kernels.
+constexpr uint32_t kPatchSlots = 3;
+
+// Workgroup size of the patch sweep: two workgroups a CU (four waves a SIMD,
+// 128 registers).
+constexpr uint32_t kSweepThreads = 512;
+
 // The MCS loop of one patch; src (shift 0) holds its region.  False if a
 // neighbour wait gave up; else the lattice is in src, with shift s.
 template <bool kPacked, bool kSeam, int kSlots, class Ctx>
@@ -1344,6 +1351,134 @@ __global__ __launch_bounds__(kPairThreads) void pair_single_kernel(
     extern __shared__ __align__(16) uint8_t smem[];
     __shared__ LdsTables<kPacked ? 8 : 32> TB;
     run_job_pair<kPacked, kProb>(J, base, smem, TB);
+}
+
+// ---------------------------------------------------------------------------
+// Patch sweep: lattices that the LDS of all CUs together cannot hold
+// ---------------------------------------------------------------------------
+struct SweepArgs {
+    const uint8_t *src;
+    uint8_t *dst;
+    uint32_t *counts;   // rows of the launch's MCS (S+1 words each, zeroed),
+                        // or null
+    uint64_t seed;
+    PatchGeom G;
+    uint32_t S, T1, T2, replica, mcs0, n_mcs, moore; // n_mcs <= G.K
+    uint32_t buf_bytes; // one copy of a region (patch_buffer_bytes)
+    const uint32_t *ab; // selection thresholds (global) or null
+    uint32_t dom[32];
+};
+
+// n_mcs MCS of every patch, from src to dst: a workgroup takes the patches
+// blockIdx.x, blockIdx.x + gridDim.x, ... one after the other, each loaded
+// with a halo that lasts for the launch's MCS (no waits between workgroups).
+// Two workgroups a CU, so that one's loads and barriers overlap the other's
+// passes (fetching the next patch's rows during the passes as well changed
+// nothing: 9548^2 139 us per MCS either way).  The counts of all its patches
+// go out in one flush.
+//
+// Bound by VALU issue (24 lane-instructions per site update, and the halo's
+// share of the updates on top), no longer by the memory traffic of a launch
+// per MCS: us per MCS in runs of 12, a launch per MCS with tiles of L / 8
+// columns or, L % 8 != 0, of words assembled from bytes / the sweep:
+//   3404^2 60 / 31, 4102^2 98 / 35, 6002^2 168 / 59, 8192^2 131 / 90,
+//   9548^2 310 / 140, 12000^2 318 / 200, 16384^2 609 / 342.
+template <bool kPacked, bool kProb>
+__global__ __launch_bounds__(kSweepThreads, 4) void patch_sweep_kernel(
+    SweepArgs a)
+{
+    constexpr int kSlots = (int)kPatchSlots;
+    extern __shared__ __align__(16) uint8_t smem[];
+    __shared__ LdsTables<kPacked ? 8 : 32> TB;
+    const PatchGeom &G = a.G;
+    const uint32_t tid = threadIdx.x, nt = blockDim.x, S = a.S;
+    const uint32_t k0 = (uint32_t)a.seed, k1 = (uint32_t)(a.seed >> 32);
+    const uint32_t cdw = patch_count_dwords(kPacked), ns = count_states(S);
+    uint32_t *const part = reinterpret_cast<uint32_t *>(smem);
+    uint8_t *const buf0 = smem + a.n_mcs * cdw * 4 + 8;
+    uint8_t *const buf1 = buf0 + a.buf_bytes;
+    uint32_t *const counts = a.counts;
+    for (uint32_t i = tid; i < a.n_mcs * cdw + a.buf_bytes / 2; i += nt)
+        part[i] = 0;
+    setup_tables(TB, a.dom, a.moore != 0, kProb ? a.ab : nullptr);
+    const auto qc = make_quad_ctx<kProb>(TB, a.T1, a.T2); // after a barrier
+    const uint32_t offs = patch_offsets(a.mcs0, a.replica, k0, k1);
+    const uint32_t RH = 2 * G.row_cut(1) + 2 * G.HR();
+    uint32_t sites = 0, gap = 0, column = ~0u;
+    // patches in columns, so that a workgroup meets a new one seldom
+    uint32_t px = blockIdx.x / G.PY, py = blockIdx.x - px * G.PY;
+    const uint32_t dx = gridDim.x / G.PY, dy = gridDim.x - dx * G.PY;
+    SweepQuads<kSlots> W;
+    PatchCount C;
+    for (; px < G.PX; px += dx + (py + dy >= G.PY ? 1u : 0u),
+                      py = py + dy >= G.PY ? py + dy - G.PY : py + dy) {
+        const Patch P = patch_at(G, py, px);
+        if (px != column) {
+            sweep_column(G, P, RH, nt, W);
+            C = patch_count_plan(G, P);
+            column = px;
+        }
+        if (P.seam != ~0u)
+            gap += P.TH * (8 - 2 * G.part());
+        sites += P.TH * 8 * P.TQ;
+        uint8_t *src = buf0, *dst = buf1;
+        sweep_load(src, a.src, G, P, W);
+        const PatchList<kSlots> &T = W.T;
+        Words rf = philox(T.c0[0], a.mcs0, kTagPass << 8, a.replica, k0, k1);
+        QuadSel sf = quad_sel(rf, qc);
+        uint32_t s = 0;
+        const auto count = [&](uint32_t m) {
+            if (!counts)
+                return;
+            uint32_t *const slots = part + m * cdw;
+            if constexpr (kPacked) {
+                if (ns == 4)
+                    patch_count_sums<4>(src, C, P.TH, slots);
+                else if (ns == 6)
+                    patch_count_sums<6>(src, C, P.TH, slots);
+                else
+                    patch_count_sums<8>(src, C, P.TH, slots);
+            } else {
+                patch_count_hist(src, C, P.TH, slots);
+            }
+        };
+        __syncthreads();
+        const auto run = [&](auto seam) __attribute__((always_inline)) {
+            constexpr bool kSeam = decltype(seam)::value;
+#pragma unroll 1
+            for (uint32_t m = 0; m < a.n_mcs; ++m) {
+                const uint32_t mt = a.mcs0 + m;
+                const uint32_t off = __builtin_amdgcn_readlane((int)offs, m);
+                if (m > 0)
+                    count(m - 1);
+#pragma unroll 1
+                for (uint32_t p = 0; p < 4; ++p) {
+                    const uint32_t w = off >> (2 * p);
+                    const PassIndex nx = p < 3 ? PassIndex{mt, p + 1}
+                                               : PassIndex{mt + 1, 0u};
+                    patch_pass<kSeam>(src, dst, s, P, T, w, PassIndex{mt, p},
+                                      nx, a.replica, k0, k1, qc, rf, sf);
+                    uint8_t *const x = src;
+                    src = dst;
+                    dst = x;
+                    s = w & 1u;
+                    __syncthreads();
+                }
+            }
+        };
+        if (P.seam != ~0u)
+            run(std::true_type());
+        else
+            run(std::false_type());
+        count(a.n_mcs - 1);
+        sweep_store(src, s, a.dst, G, P, W);
+        __syncthreads(); // 4 K passes: the state was in buf0, the next
+                         // patch's region replaces it
+    }
+    if (counts)
+        for (uint32_t m = tid >> 6; m < a.n_mcs; m += nt >> 6)
+            patch_count_flush<kPacked>(part + m * cdw, S, sites - gap, gap,
+                                       counts + (size_t)m * (S + 1));
 }
 
 // What a patch launch needs set: exchange slot 0 tagged 0, slot 1 tagged 1
@@ -2377,8 +2512,6 @@ struct PatchPlan {
     size_t lds = 0;         // dynamic LDS
 };
 
-constexpr uint32_t kPatchSlots = 3;
-
 const void *patch_kernel_fn(bool packed, bool prob, uint32_t slots)
 {
 #define ESCG_PATCH(S)                                                         \
@@ -2482,10 +2615,7 @@ PatchPlan plan_patch_uncached(uint32_t L, uint32_t S)
     }
     if (!best.ok)
         return best;
-    if (part) { // the partial quad in the middle of patch column 0
-        const uint32_t at = best.G.col_cut(1) / 2;
-        best.G.rot = (2 * Q - 1 - at) % Q;
-    }
+    best.G.set_cuts();
     best.G.slot_words = patch_slot_words(
         2 * ((Lb + best.G.PY - 1) / best.G.PY),
         (Q + best.G.PX - 1) / best.G.PX, best.G.HR(), best.G.HQ);
@@ -2583,6 +2713,136 @@ escg_status run_patch(const escg_params *p, const Derived &d,
     if (abort_out)
         launch_copy(reinterpret_cast<uint8_t *>(abort_out),
                     reinterpret_cast<const uint8_t *>(a.abort), 4, st);
+    return ESCG_OK;
+}
+
+// ---------------------------------------------------------------------------
+// Patch sweep: plan and launch
+// ---------------------------------------------------------------------------
+// Patches of at most kPatchSlots quads a thread for kSweepThreads threads, two
+// regions of two copies each in a CU's LDS, any number of patches.  More MCS a
+// launch mean fewer loads and stores and a wider halo: 16384^2, 12 MCS, us
+// per MCS with K = 1, 2, 3: 374, 356, 344 (three MCS need one more halo quad a
+// side than two); 4102^2: 44, 36, 43 (the halo costs another round of
+// patches).
+PatchPlan plan_sweep_uncached(uint32_t L, uint32_t S, uint32_t n_mcs)
+{
+    PatchPlan best;
+    const DeviceInfo di = device_info();
+    const uint32_t cus = (uint32_t)std::max(1, di.cus);
+    const size_t lds_max = (di.lds_max ? di.lds_max : 65536) / 2;
+    const bool packed = S <= 7;
+    const size_t fixed = static_lds_bytes(S) + 64;
+    double best_cost = 1e300;
+    PatchGeom G{};
+    G.L = L;
+    const uint32_t Lb = G.Lb(), Q = G.Q(), part = G.part();
+    for (uint32_t K = 1; K <= std::min(3u, n_mcs); ++K) {
+        G.K = K;
+        G.HQ = (4 * K + 1 + 7) / 8;
+        const uint32_t launches = (n_mcs + K - 1) / K;
+        for (uint32_t PX = 1; PX <= Q; ++PX) {
+            const uint32_t tq = Q / PX, TQ = (Q + PX - 1) / PX;
+            if (tq < (part ? 2 * G.HQ + 1 : G.HQ))
+                break;
+            // the tallest patch whose region fits the slots
+            const uint32_t rows = kPatchSlots * kSweepThreads /
+                                  (TQ + 2 * G.HQ); // block rows
+            if (rows < 2 * G.HR())
+                continue;
+            const uint32_t tall = rows - G.HR(); // interior block rows
+            const uint32_t PY = (Lb + tall - 1) / tall;
+            if (2 * (Lb / PY) < G.HR())
+                continue;
+            const uint32_t TH = 2 * ((Lb + PY - 1) / PY);
+            const uint32_t buf = (TH + 2 * G.HR() + 1) *
+                                     (8 * (TQ + 2 * G.HQ) + 8) + 8;
+            const size_t lds = (size_t)K * patch_count_dwords(packed) * 4 +
+                               2 * (size_t)buf;
+            if (lds + fixed > lds_max || TQ > kSweepThreads)
+                continue;
+            const uint32_t nq = (TH / 2 + G.HR()) * (TQ + 2 * G.HQ);
+            const double w = list_simd_load(nq, kSweepThreads);
+            const double rounds =
+                std::ceil((double)PY * PX / (2.0 * cus));
+            // us: two workgroups share a CU's issue; a launch's loads, tables
+            // and stores
+            const double cost =
+                rounds * (2 * 0.72 * w * n_mcs + 6.0 * launches);
+            if (cost < best_cost) {
+                best_cost = cost;
+                best.ok = true;
+                best.G = G;
+                best.G.PX = PX;
+                best.G.PY = PY;
+                best.threads = kSweepThreads;
+                best.slots = kPatchSlots;
+                best.buf_bytes = buf;
+                best.lds = lds;
+            }
+        }
+    }
+    if (best.ok)
+        best.G.set_cuts();
+    return best;
+}
+
+PatchPlan plan_sweep(uint32_t L, uint32_t S, uint32_t n_mcs)
+{
+    static std::mutex mu;
+    static std::map<std::tuple<int, uint32_t, bool, uint32_t>, PatchPlan>
+        cache;
+    n_mcs = std::min(n_mcs, 12u); // beyond, a last short launch counts little
+    int dev = 0;
+    (void)hipGetDevice(&dev);
+    const auto key = std::make_tuple(dev, L, S <= 7, n_mcs);
+    std::lock_guard<std::mutex> lk(mu);
+    auto it = cache.find(key);
+    if (it == cache.end())
+        it = cache.emplace(key, plan_sweep_uncached(L, S <= 7 ? 7u : 31u,
+                                                    n_mcs)).first;
+    return it->second;
+}
+
+// n_mcs MCS from `cur`, K a launch to and fro between `cur` and `nxt`, which
+// change places with every launch; counts: the row of the first MCS (rows
+// zeroed), or null.
+escg_status run_sweep(const escg_params *p, const Derived &d,
+                      const PatchPlan &plan, uint8_t *&cur, uint8_t *&nxt,
+                      uint32_t mcs0, uint32_t n_mcs, uint32_t *counts,
+                      hipStream_t st)
+{
+    SweepArgs a;
+    std::memset(&a, 0, sizeof(a));
+    a.seed = p->seed;
+    a.G = plan.G;
+    a.S = p->S;
+    a.T1 = d.T1;
+    a.T2 = d.T2;
+    a.replica = p->replica;
+    a.moore = (p->flags & ESCG_FLAG_MOORE) ? 1u : 0u;
+    a.buf_bytes = plan.buf_bytes;
+    a.ab = d.d_ab;
+    for (int i = 0; i < 32; ++i)
+        a.dom[i] = p->dom[i];
+    const void *fn = ESCG_KERNEL2(patch_sweep_kernel, d.small, d.prob);
+    allow_dynamic_lds(fn, plan.lds);
+    const uint32_t cus = (uint32_t)std::max(1, device_info().cus);
+    const uint32_t grid = std::min(plan.G.PY * plan.G.PX, 2 * cus);
+    uint32_t launches = (n_mcs + plan.G.K - 1) / plan.G.K;
+    for (uint32_t t = 0; t < n_mcs; t += a.n_mcs, --launches) {
+        a.src = cur;
+        a.dst = nxt;
+        a.mcs0 = mcs0 + t;
+        a.n_mcs = (n_mcs - t + launches - 1) / launches;
+        a.counts = counts ? counts + (size_t)t * (p->S + 1) : nullptr;
+        void *args[] = {&a};
+        const hipError_t e = hipLaunchKernel(
+            fn, dim3(grid), dim3(plan.threads), args, plan.lds, st);
+        if (e != hipSuccess)
+            return last_hip(e);
+        std::swap(cur, nxt);
+    }
     return ESCG_OK;
 }
 
@@ -3261,8 +3521,20 @@ escg_status step_mcs(const escg_params *p, uint8_t *d_lattice, uint32_t mcs0,
     g_last_route = ESCG_ROUTE_TILED;
     uint8_t *other = static_cast<uint8_t *>(span);
     uint8_t *cur = d_lattice, *nxt = other;
-    const TiledPlan sp = plan_step(L, S, plan_hints(p));
-    if (sp.ok) {
+    // the path taken automatically: the patch sweep, 1.4 to 2.8 times the
+    // speed; asked for, or with a tile shape or workgroup size: one launch per
+    // MCS
+    const bool chosen = p->launch.route == 0 && p->launch.tile_h == 0 &&
+                        p->launch.threads == 0;
+    const PatchPlan sweep = chosen ? plan_sweep(L, S, n_mcs) : PatchPlan{};
+    const TiledPlan sp =
+        sweep.ok ? TiledPlan{} : plan_step(L, S, plan_hints(p));
+    if (sweep.ok) {
+        s = run_sweep(p, d, sweep, cur, nxt, mcs0, n_mcs,
+                      d_counts ? d_counts + (S + 1) : nullptr, st);
+        if (s != ESCG_OK)
+            return s;
+    } else if (sp.ok) {
         StepArgs a = step_args(p, d, sp);
         for (uint32_t k = 0; k < n_mcs; ++k) {
             a.src = cur;

@@ -44,19 +44,31 @@ struct PatchGeom {
     uint32_t HQ;         // halo quads left and right, 8 HQ >= 4 K + 1
     uint32_t rot;        // global quad of rotated quad 0
     uint32_t slot_words; // 64-bit words of one patch's exchange slot
+    uint32_t rq, rr, cq, cr; // Lb / PY, Lb % PY, Q / PX, Q % PX (set_cuts)
 
     __host__ __device__ uint32_t Lb() const { return L >> 1; }
     __host__ __device__ uint32_t Q() const { return ((L >> 1) + 3) >> 2; }
     // blocks of the row's last quad (0: four)
     __host__ __device__ uint32_t part() const { return (L >> 1) & 3u; }
     __host__ __device__ uint32_t HR() const { return 4 * K; }
+    // the first parts of a cut are one longer than the others
     __host__ __device__ uint32_t row_cut(uint32_t i) const // block rows
     {
-        return i * Lb() / PY;
+        return i * rq + (i < rr ? i : rr);
     }
     __host__ __device__ uint32_t col_cut(uint32_t j) const // rotated quads
     {
-        return j * Q() / PX;
+        return j * cq + (j < cr ? j : cr);
+    }
+    // after L, PY and PX: the cuts, and the partial quad into the middle of
+    // patch column 0
+    __host__ __device__ void set_cuts()
+    {
+        rq = Lb() / PY;
+        rr = Lb() % PY;
+        cq = Q() / PX;
+        cr = Q() % PX;
+        rot = part() ? (2 * Q() - 1 - col_cut(1) / 2) % Q() : 0u;
     }
 };
 
@@ -70,11 +82,12 @@ struct Patch {
     uint32_t seam;   // region quad column of the partial quad, or ~0
 };
 
-__host__ __device__ inline Patch patch_of(const PatchGeom &G, uint32_t idx)
+__host__ __device__ inline Patch patch_at(const PatchGeom &G, uint32_t py,
+                                          uint32_t px)
 {
     Patch P;
-    P.py = idx / G.PX;
-    P.px = idx - P.py * G.PX;
+    P.py = py;
+    P.px = px;
     P.b0 = G.row_cut(P.py);
     P.TH = 2 * (G.row_cut(P.py + 1) - P.b0);
     P.c0 = G.col_cut(P.px);
@@ -83,33 +96,56 @@ __host__ __device__ inline Patch patch_of(const PatchGeom &G, uint32_t idx)
     P.NJ = P.TQ + 2 * G.HQ;
     P.LS = 8 * P.NJ + 8;
     P.seam = ~0u;
-    if (G.part()) {
-        const uint32_t Q = G.Q(), at = (Q - 1 + Q - G.rot) % Q;
+    if (G.part()) { // G.rot < Q: the partial quad's rotated number
+        const uint32_t at = G.Q() - 1 - G.rot;
         if (at >= P.c0 && at < P.c0 + P.TQ)
             P.seam = G.HQ + at - P.c0;
     }
     return P;
 }
 
+__host__ __device__ inline Patch patch_of(const PatchGeom &G, uint32_t idx)
+{
+    return patch_at(G, idx / G.PX, idx % G.PX);
+}
+
 // Bytes of one copy of the largest region: a spare word before the first row
 // (read as the column before a quad), one after each row and a spare row.
 __host__ __device__ inline uint32_t patch_buffer_bytes(const PatchGeom &G)
 {
-    uint32_t TH = 0, TQ = 0;
-    for (uint32_t i = 0; i < G.PY; ++i) {
-        const uint32_t t = 2 * (G.row_cut(i + 1) - G.row_cut(i));
-        TH = t > TH ? t : TH;
-    }
-    for (uint32_t j = 0; j < G.PX; ++j) {
-        const uint32_t t = G.col_cut(j + 1) - G.col_cut(j);
-        TQ = t > TQ ? t : TQ;
-    }
+    const uint32_t TH = 2 * G.row_cut(1), TQ = G.col_cut(1);
     return (TH + 2 * G.HR() + 1) * (8 * (TQ + 2 * G.HQ) + 8) + 8;
 }
 
+// The first 2 nb columns of a quad's row at s, the other bytes 0 (rows of
+// side L are 4-byte aligned when L % 4 == 0, where nb is 2 or 4, and 2-byte
+// otherwise).
+__device__ __forceinline__ uint2 load_quad_row(const uint8_t *s, uint32_t nb,
+                                               uint32_t L)
+{
+    uint2 v = make_uint2(0u, 0u);
+    if ((L & 3u) == 0) {
+        const uint32_t *s4 = reinterpret_cast<const uint32_t *>(s);
+        v.x = s4[0];
+        if (nb > 2)
+            v.y = s4[1];
+    } else {
+        const uint16_t *s2 = reinterpret_cast<const uint16_t *>(s);
+        v.x = s2[0];
+        if (nb > 1)
+            v.x |= (uint32_t)s2[1] << 16;
+        if (nb > 2)
+            v.y = s2[2];
+        if (nb > 3)
+            v.y |= (uint32_t)s2[3] << 16;
+    }
+    return v;
+}
+
 // Loads the region (shift 0) into `buf` from the global lattice (4-byte
-// aligned, so rows are 4-byte aligned when L % 4 == 0 and 2-byte otherwise).
-// Both copies must hold zeros beforehand.
+// aligned, so rows are 4-byte aligned when L % 4 == 0 and 2-byte otherwise);
+// gap bytes become 0.  (row, quad) advance with a carry: one division a
+// thread, and the loop's loads can be in flight together.
 __device__ inline void patch_load(uint8_t *buf, const uint8_t *g,
                                   const PatchGeom &G, const Patch &P)
 {
@@ -117,22 +153,27 @@ __device__ inline void patch_load(uint8_t *buf, const uint8_t *g,
     const uint32_t r0 = (2 * P.b0 + 4 * L - HR % L) % L;
     const uint32_t qa = (G.rot + P.c0 + 4 * Q - G.HQ) % Q;
     const uint32_t last = G.part() ? G.part() : 4u;
-    for (uint32_t i = threadIdx.x; i < P.RH * P.NJ; i += blockDim.x) {
-        const uint32_t r = i / P.NJ, j = i - r * P.NJ;
-        const uint32_t q = (qa + j) % Q, nb = q == Q - 1 ? last : 4u;
-        const uint8_t *s = g + (size_t)((r0 + r) % L) * L + 8 * q;
-        uint8_t *d = buf + r * P.LS + 8 * j;
-        if ((L & 3u) == 0) {
-            const uint32_t *s4 = reinterpret_cast<const uint32_t *>(s);
-            uint32_t *d4 = reinterpret_cast<uint32_t *>(d);
-            d4[0] = s4[0];
-            if (nb > 2)
-                d4[1] = s4[1];
-        } else {
-            const uint16_t *s2 = reinterpret_cast<const uint16_t *>(s);
-            uint16_t *d2 = reinterpret_cast<uint16_t *>(d);
-            for (uint32_t k = 0; k < nb; ++k)
-                d2[k] = s2[k];
+    uint32_t r = threadIdx.x / P.NJ, j = threadIdx.x - r * P.NJ;
+    const uint32_t dr = blockDim.x / P.NJ, dj = blockDim.x - dr * P.NJ;
+    const uint32_t n = P.RH * P.NJ;
+#pragma unroll 4
+    for (uint32_t i = threadIdx.x; i < n; i += blockDim.x) {
+        uint32_t gr = r0 + r; // < L + RH, and RH <= 3 L
+        gr = min(gr, gr - L);
+        gr = min(gr, gr - L);
+        gr = min(gr, gr - L);
+        uint32_t q = qa + j; // NJ <= 3 Q
+        q = min(q, q - Q);
+        q = min(q, q - Q);
+        q = min(q, q - Q);
+        const uint32_t nb = q == Q - 1 ? last : 4u;
+        *reinterpret_cast<uint2 *>(buf + r * P.LS + 8 * j) =
+            load_quad_row(g + (size_t)gr * L + 8 * q, nb, L);
+        j += dj;
+        r += dr;
+        if (j >= P.NJ) {
+            j -= P.NJ;
+            ++r;
         }
     }
 }
@@ -168,9 +209,11 @@ __device__ inline void patch_store(const uint8_t *buf, uint32_t s, uint8_t *g,
 {
     const uint32_t L = G.L, Q = G.Q(), HR = G.HR();
     const uint32_t last = G.part() ? G.part() : 4u;
+    uint32_t r = threadIdx.x / P.TQ, j = threadIdx.x - r * P.TQ;
+    const uint32_t dr = threads / P.TQ, dj = threads - dr * P.TQ;
     for (uint32_t i = threadIdx.x; i < P.TH * P.TQ; i += threads) {
-        const uint32_t r = i / P.TQ, j = i - r * P.TQ;
-        const uint32_t q = (G.rot + P.c0 + j) % Q;
+        uint32_t q = G.rot + P.c0 + j;
+        q = min(q, q - Q);
         const uint32_t nb = q == Q - 1 ? last : 4u;
         const uint8_t *p = buf + (HR + r) * P.LS + 8 * (G.HQ + j);
         uint2 v = *reinterpret_cast<const uint2 *>(p);
@@ -180,6 +223,12 @@ __device__ inline void patch_store(const uint8_t *buf, uint32_t s, uint8_t *g,
             v.x = (v.x << 8) | y;
         }
         store_quad_row(g + (size_t)(2 * P.b0 + r) * L + 8 * q, v, nb, L);
+        j += dj;
+        r += dr;
+        if (j >= P.TQ) {
+            j -= P.TQ;
+            ++r;
+        }
     }
 }
 
@@ -403,6 +452,107 @@ __device__ __forceinline__ void patch_pass(const uint8_t *src, uint8_t *dst,
     else
         s ? ESCG_PASS(false, true) : ESCG_PASS(false, false);
 #undef ESCG_PASS
+}
+
+// ---------------------------------------------------------------------------
+// One patch after the other in a workgroup (patch sweep): a thread's quads,
+// by their region block row and column, stay the same while the patch column
+// does, so a patch costs some hundred instructions a wave besides its passes
+// (with patch_list and patch_load for each patch, 800: as many as one MCS).
+// Every region has the rows of the tallest, RH; a shorter patch's last rows
+// only feed each other.
+// ---------------------------------------------------------------------------
+template <int kSlots>
+struct SweepQuads {
+    PatchList<kSlots> T;
+    uint32_t row[kSlots], col[kSlots];
+};
+
+template <int kSlots>
+__device__ inline void sweep_column(const PatchGeom &G, const Patch &P,
+                                    uint32_t RH, uint32_t threads,
+                                    SweepQuads<kSlots> &W)
+{
+    const uint32_t nq = (RH >> 1) * P.NJ;
+    patch_swap_selectors(G.part(), W.T);
+    W.T.n = 0;
+#pragma unroll
+    for (uint32_t i = 0; i < (uint32_t)kSlots; ++i) {
+        const uint32_t first = (threadIdx.x & ~63u) + i * threads;
+        W.T.n += first < nq ? 1u : 0u;
+        const uint32_t q = min(threadIdx.x + i * threads, nq - 1u);
+        W.row[i] = q / P.NJ;
+        W.col[i] = q - W.row[i] * P.NJ;
+        W.T.pa[i] = 2 * W.row[i] * P.LS + 8 * W.col[i];
+        W.T.part[i] = W.col[i] == P.seam;
+    }
+    W.T.n = __builtin_amdgcn_readfirstlane(W.T.n);
+}
+
+// Counter words of the patch's quads, and its region into `buf` (shift 0).
+template <int kSlots>
+__device__ __forceinline__ void sweep_load(uint8_t *buf, const uint8_t *g,
+                                           const PatchGeom &G, const Patch &P,
+                                           SweepQuads<kSlots> &W)
+{
+    const uint32_t L = G.L, Q = G.Q(), Lb = G.Lb(), hb = G.HR() >> 1;
+    const uint32_t by = P.b0 >= hb ? P.b0 - hb : P.b0 + Lb - hb;
+    uint32_t qa = G.rot + P.c0 + Q - G.HQ; // < 3 Q
+    qa = min(qa, qa - Q);
+    qa = min(qa, qa - Q);
+    const uint32_t last = G.part() ? G.part() : 4u;
+    uint2 v[kSlots][2];
+#pragma unroll
+    for (uint32_t i = 0; i < (uint32_t)kSlots; ++i) {
+        uint32_t b = by + W.row[i], q = qa + W.col[i];
+        b = min(b, b - Lb); // by < Lb, row < 2 Lb; quads alike
+        b = min(b, b - Lb);
+        q = min(q, q - Q);
+        q = min(q, q - Q);
+        W.T.c0[i] = b * Q + q;
+        const uint32_t nb = q == Q - 1 ? last : 4u;
+        const uint8_t *s = g + (size_t)(2 * b) * L + 8 * q;
+#pragma unroll
+        for (uint32_t h = 0; h < 2; ++h, s += L)
+            v[i][h] = load_quad_row(s, nb, L);
+    }
+#pragma unroll
+    for (uint32_t i = 0; i < (uint32_t)kSlots; ++i) {
+        *reinterpret_cast<uint2 *>(buf + W.T.pa[i]) = v[i][0];
+        *reinterpret_cast<uint2 *>(buf + W.T.pa[i] + P.LS) = v[i][1];
+    }
+}
+
+// Stores the interior from the copy `buf` of shift s (as patch_store).
+template <int kSlots>
+__device__ __forceinline__ void sweep_store(const uint8_t *buf, uint32_t s,
+                                            uint8_t *g, const PatchGeom &G,
+                                            const Patch &P,
+                                            const SweepQuads<kSlots> &W)
+{
+    const uint32_t L = G.L, Q = G.Q(), hb = G.HR() >> 1;
+    const uint32_t last = G.part() ? G.part() : 4u;
+#pragma unroll
+    for (uint32_t i = 0; i < (uint32_t)kSlots; ++i) {
+        const uint32_t b = W.row[i] - hb, j = W.col[i] - G.HQ;
+        if (b >= P.TH >> 1 || j >= P.TQ) // unsigned: the halo too
+            continue;
+        uint32_t q = G.rot + P.c0 + j;
+        q = min(q, q - Q);
+        const uint32_t nb = q == Q - 1 ? last : 4u;
+        uint8_t *d = g + (size_t)(2 * (P.b0 + b)) * L + 8 * q;
+#pragma unroll
+        for (uint32_t h = 0; h < 2; ++h, d += L) {
+            const uint8_t *p = buf + W.T.pa[i] + h * P.LS;
+            uint2 v = *reinterpret_cast<const uint2 *>(p);
+            if (s) {
+                const uint32_t y = p[-1];
+                v.y = __builtin_amdgcn_alignbyte(v.y, v.x, 3);
+                v.x = (v.x << 8) | y;
+            }
+            store_quad_row(d, v, nb, L);
+        }
+    }
 }
 
 // ---------------------------------------------------------------------------

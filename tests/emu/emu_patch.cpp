@@ -58,8 +58,7 @@ static int run_case(const C &c, bool moore, const double *r, int ci) {
   }
   PatchGeom G{};
   G.L = L; G.PY = c.PY; G.PX = c.PX; G.K = c.K; G.HQ = (4 * c.K + 1 + 7) / 8;
-  const uint32_t Q = G.Q();
-  if (G.part()) G.rot = (2 * Q - 1 - G.col_cut(1) / 2) % Q;
+  G.set_cuts();
   const uint32_t T = c.PY * c.PX;
   uint32_t TQmax = 0, THmax = 0, THmin = ~0u, TQmin = ~0u;
   for (uint32_t i = 0; i < T; ++i) { const Patch P = patch_of(G, i);
@@ -78,6 +77,23 @@ static int run_case(const C &c, bool moore, const double *r, int ci) {
   uint32_t abort_word = 0;
   auto bufs = [&](uint32_t t, int b) { return reinterpret_cast<uint8_t *>(sm[t].data()) + 8 + (size_t)b * nb; };
   for (uint32_t t = 0; t < T; ++t) { const Patch P = patch_of(G, t); threads(64, [&] { patch_load(bufs(t, 0), g.data(), G, P); }); }
+  { // the sweep's quads and its load and store give the same regions
+    const uint32_t RH = 2 * G.row_cut(1) + 2 * G.HR();
+    std::vector<uint8_t> out(L * L, 0xEE);
+    for (uint32_t t = 0; t < T; ++t) {
+      const Patch P = patch_of(G, t);
+      const uint32_t bd = ((RH / 2) * P.NJ + 3 * 64 - 1) / (3 * 64) * 64;
+      std::vector<uint64_t> tmp(nb / 4 + 8, 0);
+      uint8_t *buf = reinterpret_cast<uint8_t *>(tmp.data()) + 8;
+      std::vector<SweepQuads<3>> W(bd);
+      threads(bd, [&] { sweep_column(G, P, RH, bd, W[threadIdx.x]); sweep_load(buf, g.data(), G, P, W[threadIdx.x]);
+        const PatchList<3> T3 = patch_list<3>(G, P, bd);
+        for (int i = 0; i < 3; ++i) if (W[threadIdx.x].row[i] < P.RH / 2 && (T3.pa[i] != W[threadIdx.x].T.pa[i] || T3.c0[i] != W[threadIdx.x].T.c0[i] || T3.part[i] != W[threadIdx.x].T.part[i]) && threadIdx.x + i * bd < (P.RH / 2) * P.NJ) { bad++; printf("SWEEP QUAD L=%u\n", L); } });
+      for (uint32_t r = 0; r < P.RH; ++r) if (std::memcmp(buf + r * P.LS, bufs(t, 0) + r * P.LS, 8 * P.NJ)) { bad++; printf("SWEEP LOAD L=%u row %u\n", L, r); break; }
+      threads(bd, [&] { sweep_store(buf, 0, out.data(), G, P, W[threadIdx.x]); });
+    }
+    if (out != g) { bad++; printf("SWEEP STORE L=%u\n", L); }
+  }
   const uint64_t seed = 99 + L; const uint32_t rep = 2, mcs0 = 5, n = 2 * c.K + 3;
   const uint32_t k0 = (uint32_t)seed, k1 = (uint32_t)(seed >> 32);
   std::vector<uint32_t> cnt((n + 1) * (S + 1), 0);
