@@ -1499,8 +1499,8 @@ __global__ void patch_prep_kernel(uint32_t *exch, uint32_t slot_dwords,
 }
 
 // Several large lattices in one launch: job j owns workgroups
-// [wg0_j, wg0_j + T_j) (wg0_j a multiple of 8 when T_j is; workgroups in
-// the gaps exit at once) and runs its own MCS count.  The tiles of a job
+// [wg0_j, wg0_j + T_j) (wg0_j a multiple of 8 when T_j is) and runs its own
+// MCS count.  The tiles of a job
 // wait only for each other, and the launch holds no more workgroups than
 // the device keeps resident at once, so every tile becomes resident even
 // while other kernels hold CUs for a while (they never wait for this one).
@@ -3013,22 +3013,35 @@ bool aligned4(const void *p) { return ((uintptr_t)p & 3u) == 0; }
 // launch.
 constexpr uint32_t kMultiThreads = 1024;
 
-// Tile plan of a job inside a multi-job launch: the shape with the least
-// workgroup time T * (4 * busiest-SIMD quad load per pass + a fixed
-// exchange and barrier share per MCS), so large jobs take few, large tiles
-// and leave CUs for other jobs.
-TiledPlan plan_multi_uncached(uint32_t L, uint32_t S, const PlanHints &h)
+// A tile plan of a job inside a multi-job launch, and the time of its MCS in
+// units of 0.16 us: four passes of the busiest SIMD's quads and an exchange
+// (measured, 1024 threads: 34 quads 23.1 us, 22 15.9, 18 13.2, 11 7.8, 5 4.9).
+struct MultiPlan {
+    TiledPlan plan;
+    double mcs = 0;
+    uint32_t tiles() const { return plan.G.TY * plan.G.TX; }
+};
+
+// The tile plans of a job inside a multi-job launch.  The first is the shape
+// with the least workgroup time T * (4 * busiest-SIMD quad load per pass + a
+// fixed exchange and barrier share per MCS), so large jobs take few, large
+// tiles and leave CUs for other jobs; each further one (of the same kernel
+// instantiation) has more tiles and a shorter MCS than the one before, for
+// launches with workgroups to spare (level_multi).
+std::vector<MultiPlan> plan_multi_uncached(uint32_t L, uint32_t S,
+                                           const PlanHints &h)
 {
-    TiledPlan best;
+    std::vector<MultiPlan> all;
     if (L % 8 != 0 || L < 16)
-        return best;
+        return all;
     const DeviceInfo di = device_info();
     const size_t lds_max = di.lds_max ? di.lds_max : 65536;
     const uint32_t nt = kMultiThreads;
     const bool forced = h.TH != 0 && valid_shape(L, h.TH, h.TW);
     if (h.TH != 0 && !forced)
-        return best;
+        return all;
     double best_cost = 1e300;
+    size_t best = 0;
     for (uint32_t TW = 8; TW <= L; TW += 8) {
         if (L % TW || (forced && TW != h.TW))
             continue;
@@ -3047,25 +3060,43 @@ TiledPlan plan_multi_uncached(uint32_t L, uint32_t S, const PlanHints &h)
             if (!list && tiled_threads(G, nt) == 0)
                 continue;
             const double T = (double)G.TY * G.TX;
-            const double cost =
-                T * (4.0 * walk_simd_load(G, nt, list) + 24.0);
-            if (cost < best_cost) {
-                best_cost = cost;
-                best.ok = true;
-                best.G = G;
-                best.threads = nt;
-                best.lds = tiled_lds_bytes(G, list);
-                best.list = list;
+            const double load = 4.0 * walk_simd_load(G, nt, list);
+            MultiPlan m;
+            m.mcs = load + 13.0;
+            m.plan.ok = true;
+            m.plan.G = G;
+            m.plan.threads = nt;
+            m.plan.lds = tiled_lds_bytes(G, list);
+            m.plan.list = list;
+            all.push_back(m);
+            if (T * (load + 24.0) < best_cost) {
+                best_cost = T * (load + 24.0);
+                best = all.size() - 1;
             }
         }
     }
-    return best;
+    std::vector<MultiPlan> out;
+    if (all.empty())
+        return out;
+    out.push_back(all[best]);
+    std::stable_sort(all.begin(), all.end(),
+                     [](const MultiPlan &x, const MultiPlan &y) {
+                         return std::make_pair(x.tiles(), x.mcs) <
+                                std::make_pair(y.tiles(), y.mcs);
+                     });
+    for (const MultiPlan &m : all)
+        if (m.plan.list == out[0].plan.list &&
+            m.tiles() > out.back().tiles() && m.mcs < out.back().mcs)
+            out.push_back(m);
+    return out;
 }
 
-TiledPlan plan_multi(uint32_t L, uint32_t S, const PlanHints &h)
+// (Entries stay where they are for the life of the process.)
+const std::vector<MultiPlan> &plan_multi_all(uint32_t L, uint32_t S,
+                                             const PlanHints &h)
 {
     static std::mutex mu;
-    static std::map<PlanKey, TiledPlan> cache;
+    static std::map<PlanKey, std::vector<MultiPlan>> cache;
     int dev = 0;
     (void)hipGetDevice(&dev);
     const PlanKey key = std::make_tuple(dev, L, S <= 7, h.TH, h.TW, 0u);
@@ -3075,10 +3106,51 @@ TiledPlan plan_multi(uint32_t L, uint32_t S, const PlanHints &h)
         if (it != cache.end())
             return it->second;
     }
-    const TiledPlan plan = plan_multi_uncached(L, S <= 7 ? 7u : 31u, h);
+    std::vector<MultiPlan> plans =
+        plan_multi_uncached(L, S <= 7 ? 7u : 31u, h);
     std::lock_guard<std::mutex> lk(mu);
-    cache[key] = plan;
-    return plan;
+    return cache.emplace(key, std::move(plans)).first->second;
+}
+
+TiledPlan plan_multi(uint32_t L, uint32_t S, const PlanHints &h)
+{
+    const std::vector<MultiPlan> &all = plan_multi_all(L, S, h);
+    return all.empty() ? TiledPlan{} : all[0].plan;
+}
+
+// A launch lasts as long as its longest job, and the workgroups that it could
+// hold beyond its jobs' tiles would idle: the job that ends last takes more,
+// smaller tiles, again and again, until it has none or they don't fit.  24
+// jobs of L = 400, 800 and 1600 (500, 500 and 390 MCS: 2, 5 and 20 tiles each,
+// 216 workgroups, 11.9 ms, the 800s' time) end after 9.4 ms this way.
+void level_multi(const std::vector<uint32_t> &idx, const escg_params *P,
+                 const uint32_t *nm, uint32_t spare,
+                 std::vector<TiledPlan> &plans)
+{
+    std::vector<const std::vector<MultiPlan> *> all;
+    std::vector<size_t> at(idx.size(), 0);
+    for (uint32_t j : idx)
+        all.push_back(&plan_multi_all(P[j].L, P[j].S, plan_hints(&P[j])));
+    for (;;) {
+        size_t last = 0;
+        double longest = -1.0;
+        for (size_t i = 0; i < idx.size(); ++i) {
+            const double us = (*all[i])[at[i]].mcs * nm[idx[i]];
+            if (us > longest) {
+                longest = us;
+                last = i;
+            }
+        }
+        if (at[last] + 1 >= all[last]->size())
+            return;
+        const MultiPlan &more = (*all[last])[at[last] + 1];
+        const uint32_t add = more.tiles() - (*all[last])[at[last]].tiles();
+        if (add > spare)
+            return;
+        spare -= add;
+        plans[idx[last]] = more.plan;
+        ++at[last];
+    }
 }
 
 const void *persistent_multi_kernel(bool packed, bool prob, bool list)
@@ -3114,9 +3186,9 @@ uint32_t multi_capacity(const void *fn, size_t lds, uint32_t max_wgs)
 }
 
 // One multi-job launch of the jobs `idx` (same kernel instantiation; their
-// padded workgroup ranges already fit `cap`): job table, exchange areas and
+// tiles already fit `cap`): job table, exchange areas and
 // abort words in one stream-ordered allocation.
-escg_status launch_multi(const std::vector<uint32_t> &idx,
+escg_status launch_multi(std::vector<uint32_t> idx,
                          const std::vector<TiledPlan> &plans,
                          const escg_params *P, uint8_t *const *lats,
                          const uint32_t *mcs0, const uint32_t *nm, bool packed,
@@ -3124,6 +3196,11 @@ escg_status launch_multi(const std::vector<uint32_t> &idx,
 {
     const uint32_t m = (uint32_t)idx.size();
     const uint32_t Sp = packed ? 8u : 32u, abw = 2u * Sp * Sp;
+    // jobs of 8 k tiles first: they start at a multiple of 8, as their XCD
+    // bands need (xcd_tile), with no workgroups between
+    std::stable_partition(idx.begin(), idx.end(), [&](uint32_t j) {
+        return plans[j].G.TY * plans[j].G.TX % 8u == 0;
+    });
     std::vector<TiledArgs> tbl(m);
     std::vector<uint32_t> ab_all;
     if (prob)
@@ -3141,8 +3218,6 @@ escg_status launch_multi(const std::vector<uint32_t> &idx,
             std::copy(ab.begin(), ab.end(), ab_all.begin() + (size_t)i * abw);
         }
         const uint32_t T = pl.G.TY * pl.G.TX;
-        if (T % 8u == 0)
-            wg = (wg + 7u) & ~7u; // XCD bands (xcd_tile) need wg0 % 8 == 0
         TiledArgs &a = tbl[i];
         std::memset(&a, 0, sizeof(a));
         a.lattice = lats[j];
@@ -3263,10 +3338,11 @@ escg_status step_batch_persistent(uint32_t n, const escg_params *P,
                     rest.push_back(idx[k]);
                     continue;
                 }
-                need = ((T % 8u == 0) ? ((wg + 7u) & ~7u) : wg) + T;
+                need = wg + T;
             }
             if (k == idx.size() || need > cap) {
                 if (!cur.empty() && !dry_run) {
+                    level_multi(cur, P, nm, cap - wg, plans);
                     const escg_status s = launch_multi(
                         cur, plans, P, lats, mcs0, nm, packed, prob, list, st);
                     if (s != ESCG_OK)
