@@ -229,9 +229,13 @@ def tune_multi(torch, escg, L: int, S: int, K=None, ex: float = 1.0,
             continue
         if escg.last_route() != "persistent":
             continue
-        results.append({"TH": TH, "TW": TW, "copies": k,
+        # the planner's own choice is recorded as no shape: it also gives
+        # a launch's spare workgroups to the jobs that end last
+        own = shape is None
+        results.append({"TH": 0 if own else TH, "TW": 0 if own else TW,
+                        "copies": k,
                         "su_per_s": k * float(L) ** 2 * n_mcs / dt,
-                        "planner": shape is None})
+                        "planner": own})
     escg.async_status()
     if not results:
         return {}
@@ -247,16 +251,17 @@ def tune_batch(torch, escg, params: Sequence, offsets, max_mcs, mode: int,
                sides, reps: int = 2, threads=(128, 256, 384, 512),
                wg_per_cu=(0, 1, 2, 3, 4), save: bool = True) -> dict:
     """Times escg.batch_run on the given batch (its own parameters, offsets
-    and budgets) for each workgroup size and resident workgroups per CU, and
-    records the fastest under the side mix `sides`."""
+    and budgets) with the library's own choice (recorded as zeros) and for
+    each workgroup size and resident workgroups per CU, and records the
+    fastest under the side mix `sides`."""
     n = len(params)
     end = max(int(o) + int(p.L) ** 2 for o, p in zip(offsets, params))
     buf = torch.empty(end, dtype=torch.uint8, device="cuda")
     res = torch.empty(n * escg.BATCH_RESULT_WORDS, dtype=torch.int32,
                       device="cuda")
     results = []
-    for nt in threads:
-        for w in wg_per_cu:
+    for nt in (0,) + tuple(threads):
+        for w in wg_per_cu if nt else (0,):
             ps = [params[0].with_launch(threads=nt, wg_per_cu=w)] + \
                 list(params[1:])
             dt = _time(lambda: escg.batch_run(ps, offsets, buf, max_mcs, mode,
