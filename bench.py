@@ -220,7 +220,8 @@ def rps512(args, torch, escg, workloads):
     return {"workload": "rps_L512_M1e-4_10000mcs (counts every MCS)",
             "site_updates_per_s": float(w.L) ** 2 * w.mcs / wall,
             "ms_per_run": wall * 1e3, "route": escg.last_route(),
-            "tile_TH_TW_threads": escg.tile_plan(p, True),
+            "tile_TH_TW_threads": (escg.tile_plan(p, True) if autotuned
+                                   else None),
             "tile_shape_autotuned": autotuned, "reps": reps}
 
 
@@ -402,10 +403,11 @@ def main():
     tuned = autotune.apply(torch, p, "persistent")
     shape = tuned.tile if tuned is not p else None
     p = tuned
-    plan = escg.tile_plan(p, True)
+    # equal tiles only where the cache names a shape; else uneven patches
+    plan = escg.tile_plan(p, True) if shape is not None else None
     log(f"[bench] headline {w.name}: warmup {args.warmup}, steps {args.steps}, "
-        f"tile plan {plan} (autotuned: {shape is not None}, "
-        f"device {autotune.device_key(torch)})")
+        f"{f'tiles {plan}' if plan else 'patches'}, "
+        f"device {autotune.device_key(torch)}")
     h = headline(args, torch, escg, w, p)
     log(f"[bench] headline {h['value']:.4e} site-updates/s, "
         f"{h['ms_per_step']:.2f} ms/step, kernel {h['kernel_ms']:.2f} ms")
@@ -440,7 +442,8 @@ def main():
         "config": {"workload": "rpsls_L3200_M1e-5_1000mcs", "L": w.L,
                    "S": w.S, "K": list(w.K), "eps": w.ex, "mcs": w.mcs,
                    "seed": w.seed, "counts_every_mcs": True,
-                   "parallelism": "single GPU, persistent tiled kernel",
+                   "parallelism": "single GPU, persistent kernel, lattice "
+                                  "resident in the LDS of all CUs",
                    "tile_TH_TW_threads": list(plan) if plan else None,
                    "tile_shape_autotuned": shape is not None},
         "roofline": {"bound": "hbm", "achieved": achieved,
@@ -453,7 +456,8 @@ def main():
                                           / 1e9 if traffic else None),
                      "binding_limit": "alu (integer VALU issue; the lattice "
                                       "stays in LDS, see the alu block)",
-                     "kernel": "tiled_persistent_kernel",
+                     "kernel": ("tiled_persistent_kernel" if plan
+                                else "patch_kernel"),
                      "kernel_ms": h["kernel_ms"],
                      "algorithmic_bytes_per_launch":
                          BYTES_PER_SU * h["su_per_launch"]},

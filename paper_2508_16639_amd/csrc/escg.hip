@@ -10,12 +10,18 @@
 //                      workgroup barriers, counts and the stop test after
 //                      every MCS, one workgroup per job; the batch variant is
 //                      persistent and pulls jobs from a queue
+//   whole_kernel       the same for one lattice of at most 88 sites a side,
+//                      one quad a thread, counts by a wave of its own
+//   pair_*_kernel      the same with two copies of the lattice and the stop
+//                      condition tested every 32 MCS (no count rows)
 //   patch_kernel       one lattice of any even side in uneven patches, one
 //                      per CU and resident for all MCS of a call, with a halo
 //                      deep enough for several MCS between exchanges
 //   tiled_persistent_* the same with equal tiles and an exchange every MCS:
 //                      tile shapes asked for, lattices past the patch
 //                      kernel's three quads a thread, several jobs a launch
+//   patch_sweep_kernel lattices that the LDS of all CUs cannot hold: patches
+//                      with a halo for up to three MCS a launch
 //   tile_mcs_kernel    large lattices: one launch per MCS, each workgroup
 //                      stages a tile plus a 4-row / 8-column halo in LDS,
 //                      runs the four passes there (a 4-site halo covers the

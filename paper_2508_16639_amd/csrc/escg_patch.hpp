@@ -32,6 +32,15 @@
 // keep the interior exact.  With shift 1 a patch counts, publishes and
 // receives the columns one to the right of its own: all patches have the
 // same shift, so those domains tile the lattice as well.
+//
+// Measured, us per MCS with counts, before / now.  L % 8 == 0, before: equal
+// tiles, an exchange every MCS: L = 200 4.1 / 1.9, 512 3.6 / 1.9, 1600 7.2 /
+// 4.2, 3200 8.6 / 8.1; S = 8 with probabilities at 400: 6.9 / 3.1.  L % 8 != 0,
+// before: the lattice in one LDS or a launch per MCS: 300 40 / 2.1, 500 26 /
+// 2.1.  Up to L = 1000 or so latency is left (0.3 us a pass, 1 us an
+// exchange), from 2000 on vector issue: 22.1 lane-instructions per site update
+// at L = 3200 (15 of them the update itself, the halo's share most of the
+// rest), 72 % of the issue slots.
 #pragma once
 
 #include "escg_tile.hpp"

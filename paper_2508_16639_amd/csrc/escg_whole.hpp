@@ -14,6 +14,8 @@
 // is the result if it meets the stop condition, outlives them.
 // The lattice wraps inside the copies: the column past a row's last quad is
 // its first one's, the row below the last is row 0.
+// Measured at L = 64, one copy updated in place with the counts closed before
+// the next MCS / this kernel: 2.9 / 1.45 us per MCS.
 #pragma once
 
 #include "escg_patch.hpp"
