@@ -19,8 +19,8 @@ struct LdsTables {
     uint32_t selmask;             // 0x38 (von Neumann) or 0x78 (Moore)
     uint16_t rule[6 * SP * SP];   // (x', y') per action (3 used without
                                   // dominance probabilities), x, y
-    uint32_t ab[2 * SP * SP];     // selection thresholds A, B per (x, y)
-                                  // (jobs with dominance probabilities)
+    alignas(8) uint32_t ab[2 * SP * SP]; // selection thresholds {A, B} of
+                                  // (x, y) (jobs with dominance probabilities)
     uint32_t dom[32];             // dominance masks
     uint32_t cnt[64];             // count slots (S <= 7: 8 per linear
                                   // sum) or two count rows (S > 7)
@@ -208,7 +208,6 @@ __device__ inline QuadCtxT<kProb> make_quad_ctx(const LdsTables<SP> &T,
     qc.B2 = vgpr_copy(qc.B2); // the selects in block_update read B2, B3
     qc.B3 = vgpr_copy(qc.B3); // as vector operands
     qc.ab = reinterpret_cast<const uint8_t *>(T.ab);
-    qc.boff = SP * SP * 4u;
     qc.T1 = T1;
     qc.Bsel = 1u * tb;
     qc.Bo = 3u * tb;
@@ -232,7 +231,7 @@ __device__ inline void setup_tables(LdsTables<SP> &T, const uint32_t *dom,
         T.selmask = moore ? 0x78u : 0x38u;
     if (ab)
         for (uint32_t i = threadIdx.x; i < 2 * SP * SP; i += blockDim.x)
-            T.ab[i] = ab[i];
+            T.ab[i] = ab[(i & 1u) * SP * SP + (i >> 1)];
     __syncthreads();
     build_quad_luts(T.sel, T.rule, SP, T.dom, moore, ab != nullptr);
     __syncthreads();

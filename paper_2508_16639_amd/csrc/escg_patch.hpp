@@ -35,7 +35,7 @@
 //
 // Measured, us per MCS with counts, before / now.  L % 8 == 0, before: equal
 // tiles, an exchange every MCS: L = 200 4.1 / 1.9, 512 3.6 / 1.9, 1600 7.2 /
-// 4.2, 3200 8.6 / 8.1; S = 8 with probabilities at 400: 6.9 / 3.1.  L % 8 != 0,
+// 4.2, 3200 8.6 / 8.1; S = 8 with probabilities at 400: 6.9 / 2.9.  L % 8 != 0,
 // before: the lattice in one LDS or a launch per MCS: 300 40 / 2.1, 500 26 /
 // 2.1.  Up to L = 1000 or so latency is left (0.3 us a pass, 1 us an
 // exchange), from 2000 on vector issue: 22.1 lane-instructions per site update

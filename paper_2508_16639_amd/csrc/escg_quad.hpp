@@ -28,7 +28,9 @@ namespace escg {
 
 // Per-job constants of the quad update (all uniform).  kProb: the job has
 // dominance probabilities; a selection then looks up the pair's thresholds
-// A, B (LDS tables of Sp*Sp u32 each) and compares v = u - T1 with them:
+// A, B (one LDS table of Sp*Sp pairs of u32, one 8-byte read: with a table
+// each, S = 8 with probabilities took 3.4 instead of 3.2 us per MCS at L = 400
+// and 15.2 instead of 13.0 at L = 3200, S = 5 the same) and compares v = u - T1 with them:
 // v < A the selected cell wins, else v < B the neighbour wins, else nothing.
 // Those three outcomes are rule tables 3, 4, 5.
 template <bool kProb>
@@ -40,8 +42,7 @@ struct QuadCtxT {
     uint32_t W1, W2;      // word-space thresholds (w <= W1: first table ...)
     uint32_t B1, B2, B3;  // byte offsets of the three rule tables to use
     // kProb only
-    const uint8_t *ab;    // LDS: A table, then B table (Sp*Sp u32 each)
-    uint32_t boff;        // byte offset of the B table from A
+    const uint8_t *ab;    // LDS: {A, B} per (x, y) (Sp*Sp pairs of u32)
     uint32_t T1;          // selection draws are u = T1 .. T2 - 1
     uint32_t Bsel;        // byte offset of the deterministic selection table
     uint32_t Bo, so;      // outcome tables: Bo + {0, so, 2 so}
@@ -169,14 +170,12 @@ __device__ __forceinline__ uint32_t block_update_sel(uint32_t B, uint32_t w,
     uint32_t base = (w <= c.W2) ? b2 : b3;
     base = (w <= c.W1) ? b1 : base;
     if constexpr (Ctx::kProbabilistic) {
-        // 4 * (x * Sp + y): the pair's A and B entries (u32)
-        const uint32_t ai = 2u * __builtin_amdgcn_udot4(B, s.x, 0u, false);
-        const uint32_t A = *reinterpret_cast<const uint32_t *>(c.ab + ai);
-        const uint32_t Bt =
-            *reinterpret_cast<const uint32_t *>(c.ab + c.boff + ai);
+        // 8 * (x * Sp + y): the pair's thresholds A and B, one read
+        const uint32_t ai = 4u * __builtin_amdgcn_udot4(B, s.x, 0u, false);
+        const uint2 t = *reinterpret_cast<const uint2 *>(c.ab + ai);
         const uint32_t v = (w >> 8) - c.T1;
         const uint32_t so = c.so, zero = 0u;
-        const uint32_t o = c.Bo + ((v >= A) ? so : zero) + ((v >= Bt) ? so : zero);
+        const uint32_t o = c.Bo + ((v >= t.x) ? so : zero) + ((v >= t.y) ? so : zero);
         base = (base == c.Bsel) ? o : base;
     }
     const uint32_t off = __builtin_amdgcn_udot4(B, s.x, base, false);
