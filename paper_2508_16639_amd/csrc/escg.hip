@@ -2880,15 +2880,18 @@ ResidentPlan plan_resident(const escg_params *p)
 // after each chunk the host reads the counts and finds the first MCS that
 // meets the stop condition; if it lies inside the chunk, the chunk is re-run
 // from its saved start up to that MCS, so the lattice is left exactly at the
-// stopping state.  ESCG_EUNSUPPORTED (nothing but a lattice copy enqueued)
-// if the persistent launch is refused on the first chunk.
+// stopping state.  ESCG_EUNSUPPORTED if a persistent launch is refused; the
+// lattice then holds the state after `done` MCS, none of which met the stop
+// condition, and the caller goes on from there.
 escg_status run_until_persistent(const escg_params *p, const Derived &d,
                                  uint8_t *lattice, uint32_t mcs0,
                                  uint32_t max_mcs, uint32_t mode,
-                                 uint32_t *d_result, hipStream_t st)
+                                 uint32_t *d_result, hipStream_t st,
+                                 uint32_t &done)
 {
     const uint32_t L = p->L, S = p->S, N = L * L, W = S + 1;
     const uint32_t chunk_max = 1024;
+    done = 0;
     const ResidentPlan plan = plan_resident(p);
     if (!plan.ok())
         return ESCG_EUNSUPPORTED;
@@ -2962,7 +2965,7 @@ escg_status run_until_persistent(const escg_params *p, const Derived &d,
         launch_copy(saved, lattice, N, st);
         s = advance(t, n, cnt, abort_w);
         if (s != ESCG_OK)
-            break; // EUNSUPPORTED on the first chunk: the caller falls back
+            break; // refused: the lattice is still that of MCS t
         if (!fetch(n + 1)) {
             s = ESCG_EDEVICE;
             break;
@@ -2982,7 +2985,7 @@ escg_status run_until_persistent(const escg_params *p, const Derived &d,
                 launch_copy(lattice, saved, N, st);
                 s = advance(t, hit, nullptr, abort_w + 1);
                 if (s != ESCG_OK)
-                    break;
+                    break; // refused: as above
                 if (!fetch(0)) {
                     s = ESCG_EDEVICE;
                     break;
@@ -3004,6 +3007,7 @@ escg_status run_until_persistent(const escg_params *p, const Derived &d,
     }
     if (s == ESCG_OK && max_mcs == 0)
         finish(0, 0, last.data());
+    done = t;
     (void)hipFreeAsync(scr, st);
     return s;
 }
@@ -3687,9 +3691,10 @@ escg_status escg_run_until_extinction(const escg_params *p, uint8_t *d_lattice,
     const Route r = choose_route(p, st, true);
     if (r == Route::kUnsupported)
         return ESCG_EUNSUPPORTED;
+    uint32_t launched = 0; // MCS that the lattice has behind it
     if (r == Route::kPersistent) {
         s = run_until_persistent(p, d, d_lattice, mcs0, max_mcs, mode,
-                                 d_result, st);
+                                 d_result, st, launched);
         if (s != ESCG_EUNSUPPORTED) {
             g_last_route = ESCG_ROUTE_PERSISTENT;
             return s;
@@ -3711,20 +3716,19 @@ escg_status escg_run_until_extinction(const escg_params *p, uint8_t *d_lattice,
         return ESCG_ENOMEM;
     uint8_t *other = scr;
     uint32_t *stw = reinterpret_cast<uint32_t *>(scr + flags_off);
-    uint32_t *cnt2 = stw + 4; // two rows of 32 counts
+    uint32_t *cnt2 = stw + 4; // two rows of 32 counts: even and odd MCS
     launch_fill(stw, 4 + 64, 0, st);
-    s = launch_densities(d_lattice, N, S, cnt2, st);
+    s = launch_densities(d_lattice, N, S, cnt2 + (launched & 1u) * 32, st);
     if (s != ESCG_OK)
         return s;
     hipLaunchKernelGGL(check_stop_kernel, dim3(1), dim3(64), 0, st, stw, cnt2,
-                       0u, S, mode, 0u, d_result);
+                       launched & 1u, S, mode, launched, d_result);
     TileArgs a = tile_args(p, d);
     a.done = stw;
     const TiledPlan sp = plan_step(L, S, plan_hints(p));
     StepArgs sa = sp.ok ? step_args(p, d, sp) : StepArgs{};
     sa.done = stw;
     uint8_t *cur = d_lattice, *nxt = other;
-    uint32_t launched = 0;
     const uint32_t chunk = 32;
     while (launched < max_mcs) {
         uint32_t done = 0;
