@@ -76,6 +76,18 @@ typedef int32_t escg_status;
  * lattice resident in LDS: uneven patches with deep halos, or equal tiles
  * where the launch choices name a tile shape or a workgroup size, or the
  * patches would be too large). */
+/* Launches that wait.  The workgroups of a persistent launch (single job or
+ * several) wait for each other's halos, never for other work.  Each such
+ * launch holds no more workgroups than the device keeps resident and is made
+ * cooperatively: HIP runs a process's cooperative launches on a device one
+ * at a time, whatever their streams, so calls on different streams may
+ * overlap freely, and a launch becomes resident as the kernels that hold CUs
+ * (none of which waits) end.  Not covered: launches replayed from captured
+ * graphs; replay graphs that hold such calls on one stream, and not beside
+ * such calls on another.  A wait that exceeds its bound all the same
+ * (seconds; another process's waiting launches on the same device, say)
+ * leaves the lattice invalid and is reported as ESCG_ETIMEOUT by
+ * escg_async_status or by the call. */
 #define ESCG_ROUTE_LDS        1u
 #define ESCG_ROUTE_TILED      2u
 #define ESCG_ROUTE_PERSISTENT 3u
@@ -292,11 +304,9 @@ escg_status escg_batch_run(uint32_t n, const escg_params *h_params,
  *             packed whole into launches of at most max_wgs workgroups (or
  *             what the device keeps resident), longest chunk first, one
  *             launch after the other on the stream; a job with more tiles
- *             than one launch holds runs per MCS as below.  A launch's tiles
- *             wait only for each other and never for other work, so they
- *             all become resident even while other streams' kernels hold
- *             CUs for a while; a wait that exceeds its bound (seconds) is
- *             reported by escg_async_status as ESCG_ETIMEOUT.
+ *             than one launch holds, or whose launch is refused, runs per
+ *             MCS as below.  See "Launches that wait" at
+ *             ESCG_ROUTE_PERSISTENT.
  *   ESCG_ROUTE_TILED: one launch per MCS for all jobs: the tiles of every
  *             job still running form one grid, so lattices too small to
  *             fill the GPU on their own share it.

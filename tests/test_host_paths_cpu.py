@@ -35,6 +35,60 @@ def test_refused_chunk_is_not_started_over(fake_so, refuse, stop, done):
     fake_hip.run(fake_so, __file__, "refused_chunk", refuse, stop, done)
 
 
+WAITING = ("patch_kernel", "tiled_persistent_kernel",
+           "tiled_persistent_multi_kernel")
+
+
+def waiting_launches(f):
+    """Launches whose workgroups wait for each other are cooperative (ordered
+    against each other by the runtime) and fit the device; the others are
+    ordinary."""
+    def check(*kinds):
+        for x in f.launches():
+            waits = any(k in x.name for k in WAITING)
+            assert x.cooperative == waits, x
+            assert not waits or x.grid <= 256, x
+        for k in kinds:
+            assert f.names(k), (k, f.launches())
+
+    f.reset()
+    for p in (f.params(300), f.params(512), f.params(3200, S=9),
+              f.params(3600), f.params(512, tile=(32, 32))):
+        assert f.step(p, 50) == 0
+    check("patch_kernel", "tiled_persistent_kernel")
+    for wgs in (0, 40):
+        f.reset()
+        ps = [f.params(400 << (j % 3), S=(3, 9)[j % 2]) for j in range(24)]
+        ps[0] = ps[0].with_launch(max_wgs=wgs)
+        assert f.step_batch(ps, [500] * 24) == 0
+        assert f.lib.escg_last_route() == f.escg.ROUTE_PERSISTENT
+        check("tiled_persistent_multi_kernel")
+        assert not wgs or all(x.grid <= wgs for x in f.names("multi"))
+
+
+def refused_multi(f, refuse):
+    """Jobs of a refused multi-job launch go out per MCS, all of their MCS;
+    the launches before it stay."""
+    f.reset(refuse=refuse)
+    # S <= 7 and S > 7: two launches
+    ps = [f.params(400), f.params(136, S=9), f.params(800)]
+    assert f.step_batch(ps, [6, 5, 4]) == 0
+    assert len(f.names("multi")) == refuse
+    steps = f.names("tiled_step_batch_kernel")
+    assert len(steps) == {0: 11, 1: 6, 2: 0}[refuse], steps
+    assert f.lib.escg_last_route() == (f.escg.ROUTE_PERSISTENT if refuse
+                                       else f.escg.ROUTE_TILED)
+
+
+def test_launches_that_wait_are_cooperative(fake_so):
+    fake_hip.run(fake_so, __file__, "waiting_launches")
+
+
+@pytest.mark.parametrize("refuse", [0, 1, 2])
+def test_refused_multi_job_launch_runs_per_mcs(fake_so, refuse):
+    fake_hip.run(fake_so, __file__, "refused_multi", refuse)
+
+
 if __name__ == "__main__":
     globals()[sys.argv[2]](fake_hip.Fake(sys.argv[1]),
                            *map(int, sys.argv[3:]))
