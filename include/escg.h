@@ -102,9 +102,9 @@ typedef int32_t escg_status;
  *             job: LDS needs L <= escg_batch_max_L(S), persistent needs
  *             L % 8 == 0 and a tile plan whose tiles are all resident).
  *             Automatic: persistent if L % 8 == 0 and L >= 72, or L > 88
- *             (not under stream capture, and not in a run until extinction
- *             that one workgroup's LDS can hold), while the lattice fits
- *             the LDS of all compute units; else the
+ *             (not in a run until extinction that one workgroup's LDS can
+ *             hold), while the lattice fits the LDS of all compute units
+ *             (under stream capture only with such a tile plan); else the
  *             whole lattice in one workgroup's LDS if it fits, else tiled
  *             launches.
  *   tile_h, tile_w   tile shape of the tiled paths (both 0: the planner's

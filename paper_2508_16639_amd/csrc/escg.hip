@@ -3393,8 +3393,9 @@ escg_status step_batch_persistent(uint32_t n, const escg_params *P,
 // its launch choice: forced, or automatic (persistent for L >=
 // kPersistentMinL when a resident plan exists, else the whole lattice in one
 // workgroup's LDS when it fits, else per-MCS tiled launches).  Forcing the
-// persistent path needs L % 8 == 0.  A lattice with L % 8 != 0 keeps to
-// ordinary launches under stream capture (a cooperative one may refuse it),
+// persistent path needs a plan of equal resident tiles, and so L % 8 == 0
+// (some such sides have none: 8 times a prime).  A lattice without one keeps
+// to ordinary launches under stream capture (a cooperative one may refuse it),
 // and, where it fits the LDS, in a run until extinction (`until`), which is
 // asynchronous there.  At L = 90 a patch MCS takes 2.1 us and the LDS
 // kernel's 7.7, at L = 300 2.1 and 39.
@@ -3404,16 +3405,18 @@ Route choose_route(const escg_params *p, hipStream_t st, bool until)
 {
     const uint32_t L = p->L, S = p->S;
     const bool fits_lds = L <= lds_max_L(S);
-    const auto plan_ok = [&] {
-        return (L & 7u) == 0 && plan_resident(p).ok();
-    };
-    const auto ragged_ok = [&] {
-        if (L <= kWholeMaxL || (until && fits_lds))
-            return false;
+    const auto tiles_ok = [&] { return plan_tiled(L, S, plan_hints(p)).ok; };
+    const auto capturing = [&] {
         hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
         if (hipStreamIsCapturing(st, &cs) != hipSuccess)
             (void)hipGetLastError();
-        return cs == hipStreamCaptureStatusNone && plan_resident(p).ok();
+        return cs != hipStreamCaptureStatusNone;
+    };
+    const auto resident_ok = [&] {
+        if ((L & 7u) == 0 ? L < kPersistentMinL
+                          : L <= kWholeMaxL || (until && fits_lds))
+            return false;
+        return plan_resident(p).ok() && (!capturing() || tiles_ok());
     };
     switch (p->launch.route) {
     case ESCG_ROUTE_LDS:
@@ -3421,9 +3424,9 @@ Route choose_route(const escg_params *p, hipStream_t st, bool until)
     case ESCG_ROUTE_TILED:
         return Route::kTiled;
     case ESCG_ROUTE_PERSISTENT:
-        return plan_ok() ? Route::kPersistent : Route::kUnsupported;
+        return tiles_ok() ? Route::kPersistent : Route::kUnsupported;
     default:
-        if ((L & 7u) == 0 ? L >= kPersistentMinL && plan_ok() : ragged_ok())
+        if (resident_ok())
             return Route::kPersistent;
         return fits_lds ? Route::kLds : Route::kTiled;
     }

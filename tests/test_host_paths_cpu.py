@@ -89,6 +89,30 @@ def test_refused_multi_job_launch_runs_per_mcs(fake_so, refuse):
     fake_hip.run(fake_so, __file__, "refused_multi", refuse)
 
 
+def no_tile_plan(f):
+    """Sides whose only divisors that are multiples of 8 are 8 and L have
+    patches but no equal resident tiles: the persistent path is refused when
+    asked for and no cooperative launch is captured; sides with tiles, and
+    calls that leave the choice to the library, are as ever."""
+    for L, tiles in ((8, False), (2056, False), (3208, False), (16, True),
+                     (512, True), (3200, True)):
+        for S in (3, 9):
+            want = 0 if tiles else f.escg.EUNSUPPORTED
+            q = f.params(L, S=S, route="persistent")
+            f.reset(words=S + 1)
+            assert f.step(q, 6) == want and f.until(q, 6) == want, (L, S)
+            assert tiles or not f.launches()
+            for capture in (False, True):
+                f.reset(capture=capture)
+                assert f.step(f.params(L, S=S), 6) == 0
+                waits = [x for x in f.launches() if x.cooperative]
+                assert bool(waits) == (L >= 72 and (tiles or not capture)), L
+
+
+def test_sides_without_a_tile_plan(fake_so):
+    fake_hip.run(fake_so, __file__, "no_tile_plan")
+
+
 if __name__ == "__main__":
     globals()[sys.argv[2]](fake_hip.Fake(sys.argv[1]),
                            *map(int, sys.argv[3:]))
