@@ -13,7 +13,7 @@
 //   whole_kernel       the same for one lattice of at most 88 sites a side,
 //                      one quad a thread, counts by a wave of its own
 //   pair_*_kernel      the same with two copies of the lattice and the stop
-//                      condition tested every 32 MCS (no count rows)
+//                      condition tested in windows of MCS (no count rows)
 //   patch_kernel       one lattice of any even side in uneven patches, one
 //                      per CU and resident for all MCS of a call, with a halo
 //                      deep enough for several MCS between exchanges
@@ -1170,12 +1170,37 @@ __global__ __launch_bounds__(kWholeThreads) void whole_kernel(JobDev J,
 // 3.2 -> 2.5.
 constexpr uint32_t kPairThreads = 1024;
 
-// MCS between two tests of the stop condition.  A species that is extinct
-// stays extinct, so a condition that holds at a test has held since some MCS
-// after the last test: the job goes back to the state of that test (kept in
-// its lattice's place in global memory) and tests after every MCS.  Counting
-// after every MCS took a tenth of the instructions.
-constexpr uint32_t kPairCheck = 32;
+// The stop condition of the state in `src` (nw words), by the species that are
+// there, not by their counts: a wave reads words until it has seen enough of
+// them, one read almost always, so a test costs little more than its barrier
+// (counting the sites took as long as an MCS at L = 64).  seen: two LDS words,
+// zeroed before the first test; k: 0 and 1 in turn.
+__device__ __forceinline__ bool pair_stop(const uint8_t *src, uint32_t nw,
+                                          uint32_t S, uint32_t mode,
+                                          uint32_t *seen, uint32_t k)
+{
+    const uint32_t all = (2u << S) - 2u;
+    const auto goes_on = [&](uint32_t m) {
+        m &= all;
+        return mode == ESCG_STOP_FIRST_EXTINCTION ? m == all
+                                                  : (m & (m - 1u)) != 0;
+    };
+    uint32_t m = 0;
+    for (uint32_t i = threadIdx.x; (i & ~63u) < nw; i += blockDim.x) {
+        uint32_t b = 0;
+        if (i < nw)
+            b = species_bits(*reinterpret_cast<const uint2 *>(src + 8 * i));
+        m |= wave_or(b);
+        if (goes_on(m))
+            break;
+    }
+    if ((threadIdx.x & 63u) == 0)
+        atomicOr(seen + k, m);
+    __syncthreads();
+    if (threadIdx.x == 0) // between this test's barrier and the next test
+        seen[k ^ 1u] = 0;
+    return !goes_on(__builtin_amdgcn_readfirstlane(seen[k]));
+}
 
 template <bool kPacked, bool kProb>
 __device__ __forceinline__ void run_job_pair(const JobDev &J, uint8_t *base, uint8_t *smem,
@@ -1187,7 +1212,7 @@ __device__ __forceinline__ void run_job_pair(const JobDev &J, uint8_t *base, uin
     const uint32_t k0 = (uint32_t)J.seed, k1 = (uint32_t)(J.seed >> 32);
     uint8_t *src = smem, *dst = smem + size;
     uint8_t *const g = base + J.lat_off;
-    uint32_t s = 0, t = 0, step = kPairCheck; // s: shift of src
+    uint32_t s = 0, t = 0; // s: shift of src
 
     const auto zero = [&] {
         for (uint32_t i = tid; i < size / 8; i += nt)
@@ -1217,13 +1242,86 @@ __device__ __forceinline__ void run_job_pair(const JobDev &J, uint8_t *base, uin
     setup_tables(TB, J.dom, J.moore != 0, kProb ? J.ab : nullptr);
     const auto qc = make_quad_ctx<kProb>(TB, J.T1, J.T2); // after a barrier
 
-    // counts of the state in src: S <= 7 into c[] (uniform), else into
-    // TB.cnt[0..S]; returns the stop test (TB.cnt: slots, cleared by
-    // setup_tables, or the counts)
-    uint32_t c[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-    uint32_t prev[7] = {0, 0, 0, 0, 0, 0, 0};
-    const uint32_t ns = count_states(S);
-    const auto test = [&] {
+    const uint32_t replica = J.replica, mcs0 = J.mcs0, mode = J.mode;
+    uint32_t tests = 0;
+    const auto test = [&]() __attribute__((always_inline)) {
+        return mode != ESCG_STOP_NONE &&
+               pair_stop(src, nw, S, mode, TB.cnt + 62, tests++ & 1u);
+    };
+    bool stop = test();
+    bool replay = false; // the MCS since the last test, one at a time
+    // (inline: a call would keep the lattice's state in scratch memory)
+    const auto run = [&](auto slots) __attribute__((always_inline)) {
+        constexpr int kSlots = decltype(slots)::value;
+        WholeSlots<kSlots> W = whole_slots<kSlots>(G, nt);
+        uint32_t offs = 0;
+        Words rf;
+        QuadSel sf;
+        const auto start = [&] { // the draws of MCS t
+            offs = patch_offsets(mcs0 + (t & ~63u), replica, k0, k1);
+            rf = philox(W.c0[0], mcs0 + t, kTagPass << 8, replica, k0, k1);
+            sf = quad_sel(rf, qc);
+        };
+        start();
+        while (t < J.max_mcs) {
+            const uint32_t n = min(mode == ESCG_STOP_NONE ? J.max_mcs
+                                   : replay               ? 1u
+                                                          : pair_window(t),
+                                   J.max_mcs - t);
+#pragma unroll 1
+            for (uint32_t m = 0; m < n; ++m, ++t) {
+                if ((t & 63u) == 0)
+                    offs = patch_offsets(mcs0 + t, replica, k0, k1);
+                const uint32_t off =
+                    __builtin_amdgcn_readlane((int)offs, t & 63u);
+                const uint32_t mt = mcs0 + t;
+#pragma unroll 2
+                for (uint32_t p = 0; p < 4; ++p) {
+                    const uint32_t w = off >> (2 * p);
+                    whole_pass_slots<kSlots>(
+                        src, dst, s, G, W, w, PassIndex{mt, p},
+                        p < 3 ? PassIndex{mt, p + 1} : PassIndex{mt + 1, 0u},
+                        replica, k0, k1, qc, rf, sf);
+                    uint8_t *const x = src;
+                    src = dst;
+                    dst = x;
+                    s = w & 1u;
+                    __syncthreads();
+                }
+            }
+            stop = test();
+            if (stop && n == 1)
+                break;
+            if (stop) { // back to the last test
+                t -= n;
+                replay = true;
+                stop = false;
+                __threadfence(); // the stores of that state, by all threads
+                zero();
+                whole_load(src, g, G);
+                s = 0;
+                start();
+                __syncthreads();
+            } else if (!replay && t < J.max_mcs && pair_window(t) > 1) {
+                store();
+            }
+        }
+    };
+    if (!stop)
+        switch (((L >> 1) * G.Q() + nt - 1) / nt) { // quads a thread
+        case 1: run(std::integral_constant<int, 1>()); break;
+        case 2: run(std::integral_constant<int, 2>()); break;
+        case 3: run(std::integral_constant<int, 3>()); break;
+        case 4: run(std::integral_constant<int, 4>()); break;
+        default: run(std::integral_constant<int, 5>()); break;
+        }
+    store();
+    if (J.result) {
+        // counts: S <= 7 in c[] (uniform), else in TB.cnt[0..S] (TB.cnt: slots,
+        // cleared by setup_tables but for the tests' words past them)
+        uint32_t c[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+        uint32_t prev[7] = {0, 0, 0, 0, 0, 0, 0};
+        const uint32_t ns = count_states(S);
         const uint32_t *src32 = reinterpret_cast<const uint32_t *>(src);
         if constexpr (kPacked) {
             if (ns == 4) {
@@ -1239,84 +1337,13 @@ __device__ __forceinline__ void run_job_pair(const JobDev &J, uint8_t *base, uin
                 __syncthreads();
                 lds_count_close<8>(TB.cnt, prev, L * L, 0, c);
             }
-            __syncthreads();
-            return stop_met8(c, S, J.mode);
         } else {
-            if (tid < 32) // gap bytes count as zeros
-                TB.cnt[tid] = tid == 0 ? L * L - size : 0u;
+            if (tid == 0) // gap bytes count as zeros
+                TB.cnt[0] = L * L - size;
             __syncthreads();
             count_dwords_wide(src32, size / 4, S, TB.cnt);
             __syncthreads();
-            const bool met = stop_met(TB.cnt, S, J.mode);
-            __syncthreads();
-            return met;
         }
-    };
-    // n <= 64 MCS (a call would keep the lattice's state in scratch memory)
-    const auto advance = [&](uint32_t n, auto slots)
-        __attribute__((always_inline)) {
-        constexpr int kSlots = decltype(slots)::value;
-        WholeSlots<kSlots> W = whole_slots<kSlots>(G, nt);
-        const uint32_t t0 = J.mcs0 + t, replica = J.replica;
-        const uint32_t offs = patch_offsets(t0, replica, k0, k1);
-        Words rf = philox(W.c0[0], t0, kTagPass << 8, replica, k0, k1);
-        QuadSel sf = quad_sel(rf, qc);
-#pragma unroll 1
-        for (uint32_t m = 0; m < n; ++m) {
-            const uint32_t off = __builtin_amdgcn_readlane((int)offs, m);
-#pragma unroll 2
-            for (uint32_t p = 0; p < 4; ++p) {
-                const uint32_t w = off >> (2 * p);
-                whole_pass_slots<kSlots>(
-                    src, dst, s, G, W, w, PassIndex{t0 + m, p},
-                    p < 3 ? PassIndex{t0 + m, p + 1}
-                          : PassIndex{t0 + m + 1, 0u},
-                    replica, k0, k1, qc, rf, sf);
-                uint8_t *const x = src;
-                src = dst;
-                dst = x;
-                s = w & 1u;
-                __syncthreads();
-            }
-        }
-    };
-    const uint32_t slots = ((L >> 1) * G.Q() + nt - 1) / nt;
-    bool stop = test();
-    if (J.init && J.mode != ESCG_STOP_NONE && !stop && J.max_mcs > 0)
-        store();
-    while (!stop && t < J.max_mcs) {
-        const uint32_t n = J.mode == ESCG_STOP_NONE
-                               ? min(64u, J.max_mcs - t)
-                               : min(step, J.max_mcs - t);
-        switch (slots) {
-        case 1: advance(n, std::integral_constant<int, 1>()); break;
-        case 2: advance(n, std::integral_constant<int, 2>()); break;
-        case 3: advance(n, std::integral_constant<int, 3>()); break;
-        case 4: advance(n, std::integral_constant<int, 4>()); break;
-        default: advance(n, std::integral_constant<int, 5>()); break;
-        }
-        t += n;
-        if (J.mode == ESCG_STOP_NONE) {
-            if (t == J.max_mcs)
-                (void)test(); // the counts
-            continue;
-        }
-        stop = test();
-        if (stop && n > 1) { // back to the last test, one MCS at a time
-            t -= n;
-            step = 1;
-            stop = false;
-            __threadfence(); // the stores of that state, by all threads
-            zero();
-            whole_load(src, g, G);
-            s = 0;
-            __syncthreads();
-        } else if (!stop && step > 1 && t < J.max_mcs) {
-            store();
-        }
-    }
-    store();
-    if (J.result) {
         for (uint32_t i = tid; i < J.result_words; i += nt) {
             uint32_t v = 0;
             if (i == 0)
@@ -2088,8 +2115,8 @@ escg_status launch_lds_single(const JobDev &J, bool small, uint8_t *base,
 {
     if (J.L <= kWholeMaxL)
         return launch_whole(J, small, base, st);
-    // without count rows the counts of a test every 32 MCS do (L = 100:
-    // 9.9 -> 2.6 us per MCS, L = 250: 33 -> 11)
+    // without count rows two copies do, the stop condition tested now and
+    // then (L = 100: 9.9 -> 2.6 us per MCS, L = 250: 33 -> 11)
     const bool pair =
         !J.counts && pair_fits(lds_job_bytes(J.L, J.S), J.S);
     const size_t lds = (pair ? 2 : 1) * lds_job_bytes(J.L, J.S);
@@ -4154,7 +4181,11 @@ escg_status escg_batch_run(uint32_t n, const escg_params *h_params,
         pair = two_copies < in_place;
     }
     const size_t lds = pair ? 2 * lds_need : lds_need;
-    const uint32_t nt = pair         ? kPairThreads
+    // (two copies: a thread for every quad, as far as they go; waves without
+    // quads would only lengthen the barriers: 16 jobs of L = 8, 1000 MCS,
+    // 2.0 ms with 1024 threads, 1.7 with 64, 2.5 in place)
+    const uint32_t nt = pair ? std::min(kPairThreads,
+                                        (whole_quads(Lmax) + 63) / 64 * 64)
                         : ln.threads ? std::min(ln.threads, 512u)
                                      : lds_threads(Lmax);
     const void *fn = pair ? ESCG_KERNEL2(pair_batch_kernel, all_small, prob)

@@ -317,6 +317,28 @@ __device__ __forceinline__ uint32_t wave_sum(uint32_t v)
     return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
 }
 
+// The bitwise or of v over a wave, the same way.
+__device__ __forceinline__ uint32_t wave_or(uint32_t v)
+{
+    v |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xF, 0xF, true);
+    v |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xF, 0xF, true);
+    v |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xF, 0xF, true);
+    v |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xF, 0xF, true);
+    v |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xA, 0xF, false);
+    v |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xC, 0xF, false);
+    return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
+}
+
+// Bits of the values (below 32) of a word's eight bytes.
+__device__ __forceinline__ uint32_t species_bits(uint2 v)
+{
+    uint32_t b = 0;
+#pragma unroll
+    for (uint32_t k = 0; k < 4; ++k)
+        b |= 1u << ((v.x >> (8 * k)) & 31u) | 1u << ((v.y >> (8 * k)) & 31u);
+    return b;
+}
+
 // Species counting for values 0..7 (densities_kernel): v_perm with the byte
 // table {1, 2, 4, ..., 128} maps every byte of a dword to its one-hot code
 // (bytes 12, used as padding, map to 0), so the count of species s in the

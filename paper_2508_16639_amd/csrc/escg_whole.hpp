@@ -225,6 +225,21 @@ __device__ __forceinline__ void whole_pass_slots(
 #undef ESCG_PASS
 }
 
+// MCS from the test of the stop condition after MCS t to the next one.  A
+// species that is extinct stays extinct, so a condition that holds at a test
+// has held since some MCS after the last test: the job goes back to the state
+// of that test (kept in its lattice's place in global memory) and tests after
+// every MCS.  So a stop at t costs at most t / 16 MCS run twice and as many
+// past it.  Up to t = 128 every MCS is tested and no state is kept: the test
+// costs little (pair_stop), the copy of the state half an MCS at L = 256.
+// Batches that stop after 25 MCS (64 of L = 256, 512 of L = 192, 16 of L = 8),
+// us: first test after 32 MCS 1048, 3177, 349; in-place kernel, which tests
+// after every MCS, 789, 2447, 223; now 652, 2517, 207.
+__host__ __device__ inline uint32_t pair_window(uint32_t t)
+{
+    return t < 128u ? 1u : min(32u, t / 16u);
+}
+
 // Loads the lattice (shift 0) into `buf`, which holds zeros.
 __device__ inline void whole_load(uint8_t *buf, const uint8_t *g,
                                   const WholeGeom &G)

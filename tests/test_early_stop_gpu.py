@@ -1,0 +1,95 @@
+"""Runs that stop early on the kernel that tests the stop condition in windows:
+no slower than the kernel that tests after every MCS, and exact where the stop
+lies in a window of several MCS."""
+import numpy as np
+import pytest
+
+import oracle as O
+from paper_2508_16639_amd import escg
+from paper_2508_16639_amd.workloads import random_lattice
+from tests.gpu_util import dev, host, pair
+from tests.test_extinction_gpu import _batch, oracle_until
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+
+def takeover(S):
+    """Species 1 beats all others, which do not interact."""
+    D = np.zeros((S, S), np.uint8)
+    D[0, 1:] = 1
+    return D
+
+
+@pytest.mark.parametrize("n", [64, 512])
+@pytest.mark.parametrize("L", [16, 128, 192, 256])
+def test_early_stops_cost_no_more_than_testing_every_mcs(L, n):
+    """The kernel of the library's choice against the one that tests after
+    every MCS (a workgroup size asked for selects it): at most 15 % longer,
+    of which a stop within 128 MCS allows for nothing but timing noise."""
+    ps = [pair(L, 3, None, 0.2, seed=11, replica=i, D=takeover(3))[0]
+          for i in range(n)]
+    offs = [i * L * L for i in range(n)]
+    buf = torch.empty(n * L * L, dtype=torch.uint8, device="cuda:0")
+    res = torch.empty(n * escg.BATCH_RESULT_WORDS, dtype=torch.int32,
+                      device="cuda:0")
+    best = []
+    for kw in ({}, {"threads": 256 if L <= 128 else 512}):
+        qs = [ps[0].with_launch(**kw)] + ps[1:]
+        ms = []
+        for _ in range(6):
+            a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            a.record()
+            escg.batch_run(qs, offs, buf, [2000] * n,
+                           escg.STOP_FIRST_EXTINCTION, True, res)
+            b.record()
+            torch.cuda.synchronize()
+            ms.append(a.elapsed_time(b))
+        best.append(min(ms))
+    t = host(res).reshape(n, -1)[:, 1]
+    assert t.max() < 128, t.max()
+    assert best[0] <= 1.15 * best[1], best
+
+
+@pytest.mark.parametrize("S", [3, 9])
+@pytest.mark.parametrize("L,sel", [(90, 0.06), (98, 0.02), (126, 0.03),
+                                   (222, 0.04)])
+def test_stops_inside_a_window(L, S, sel):
+    p, j = pair(L, S, None, 0.5, sel, 1.0, seed=5, replica=L, D=takeover(S),
+                route="lds")
+    g0 = j.init()
+    full = oracle_until(j, g0.copy(), 3, 3000, escg.STOP_FIRST_EXTINCTION)
+    t = int(full[1])
+    assert full[0] == 1 and t > 144, full
+    for cap in (t - 1, t, t + 1, 3000):
+        ref = g0.copy()
+        r = oracle_until(j, ref, 3, cap, escg.STOP_FIRST_EXTINCTION)
+        lat = dev(g0)
+        res = torch.full((S + 3,), -1, dtype=torch.int32, device="cuda:0")
+        escg.run_until_extinction(p, lat, 3, cap, escg.STOP_FIRST_EXTINCTION,
+                                  res)
+        assert escg.last_route() == "lds"
+        assert np.array_equal(host(res), r), (cap, host(res), r)
+        assert np.array_equal(host(lat), ref), cap
+
+
+@pytest.mark.parametrize("mode", [escg.STOP_FIRST_EXTINCTION,
+                                  escg.STOP_MONOCULTURE])
+@pytest.mark.parametrize("init", [True, False])
+def test_batch_stops_inside_windows(init, mode):
+    jobs = []
+    for i in range(8):
+        L = [34, 90, 100, 128][i % 4]
+        p, j = pair(L, 3, None, 0.5, 0.01 * (1 + i % 5), 1.0, seed=50, replica=i,
+                    D=takeover(3))
+        jobs.append((p, j, 2500,
+                     None if init else random_lattice(L, 3, seed=i)))
+    lats, r = _batch(jobs, mode, init, [7 * i for i in range(8)])
+    stops = []
+    for i, ((p, j, cap, g0), lat, rr) in enumerate(zip(jobs, lats, r)):
+        g = j.init() if init else g0.copy()
+        ref = oracle_until(j, g, 7 * i, cap, mode)
+        stops.append(int(ref[1]))
+        assert np.array_equal(rr[:6], ref), (p.L, rr, ref)
+        assert np.array_equal(lat, g), p.L
+    assert sum(144 < t < 2500 for t in stops) >= 3, stops
