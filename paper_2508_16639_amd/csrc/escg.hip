@@ -2685,15 +2685,23 @@ PatchPlan plan_patch(uint32_t L, uint32_t S)
     return plan;
 }
 
-// Scratch of a patch launch: two exchange slots per patch and the abort word.
-size_t patch_scratch_bytes(const PatchPlan &plan)
+// Words of an exchange slot of all patches in a run of n_mcs MCS: none where
+// the run ends before its first exchange (allocated anew after a
+// synchronisation, the slots of L = 700 cost a call of one MCS 25 us of 73).
+uint32_t patch_exchange_words(const PatchPlan &plan, uint32_t n_mcs)
 {
     const PatchGeom &G = plan.G;
-    return 2 * (size_t)G.PY * G.PX * G.slot_words * 8 + 256;
+    return n_mcs <= G.K ? 0u : G.PY * G.PX * G.slot_words;
+}
+
+// Scratch of a patch launch: two exchange slots per patch and the abort word.
+size_t patch_scratch_bytes(const PatchPlan &plan, uint32_t n_mcs)
+{
+    return 2 * (size_t)patch_exchange_words(plan, n_mcs) * 8 + 256;
 }
 
 // n_mcs > 0 MCS with the patch kernel; counts: every row, row 0 included.
-// area: patch_scratch_bytes(plan).  As run_tiled_persistent otherwise.
+// area: patch_scratch_bytes(plan, n_mcs).  As run_tiled_persistent otherwise.
 escg_status run_patch(const escg_params *p, const Derived &d,
                       const PatchPlan &plan, uint8_t *lattice, uint32_t mcs0,
                       uint32_t n_mcs, uint32_t *counts, hipStream_t st,
@@ -2705,7 +2713,7 @@ escg_status run_patch(const escg_params *p, const Derived &d,
     std::memset(&a, 0, sizeof(a));
     a.lattice = lattice;
     a.exch = reinterpret_cast<uint64_t *>(area);
-    a.xstride = T * G.slot_words;
+    a.xstride = patch_exchange_words(plan, n_mcs);
     a.abort = reinterpret_cast<uint32_t *>(a.exch + 2 * (size_t)a.xstride);
     a.counts = counts;
     a.seed = p->seed;
@@ -2886,9 +2894,10 @@ struct ResidentPlan {
     PatchPlan patch;
     TiledPlan tiled;
     bool ok() const { return patch.ok || tiled.ok; }
-    size_t scratch_bytes() const
+    size_t scratch_bytes(uint32_t n_mcs) const // of a run of n_mcs MCS or less
     {
-        return patch.ok ? patch_scratch_bytes(patch) : exchange_bytes(tiled);
+        return patch.ok ? patch_scratch_bytes(patch, n_mcs)
+                        : exchange_bytes(tiled);
     }
 };
 
@@ -2928,8 +2937,8 @@ escg_status run_until_persistent(const escg_params *p, const Derived &d,
     const size_t lat_off = (cnt_bytes + 8 + 255) & ~(size_t)255;
     const size_t ex_off = (lat_off + N + 255) & ~(size_t)255;
     uint8_t *scr = nullptr;
-    if (hipMallocAsync((void **)&scr, ex_off + plan.scratch_bytes(), st) !=
-        hipSuccess)
+    if (hipMallocAsync((void **)&scr, ex_off + plan.scratch_bytes(max_mcs),
+                       st) != hipSuccess)
         return ESCG_ENOMEM;
     uint32_t *cnt = reinterpret_cast<uint32_t *>(scr);
     uint32_t *abort_w = reinterpret_cast<uint32_t *>(scr + cnt_bytes);
@@ -3589,7 +3598,8 @@ escg_status step_mcs(const escg_params *p, uint8_t *d_lattice, uint32_t mcs0,
             r == Route::kLds ? 0
                              : Arena::round(persistent
                                                 ? std::max<size_t>(
-                                                      plan.scratch_bytes(), N)
+                                                      plan.scratch_bytes(n_mcs),
+                                                      N)
                                                 : N);
         if (n_mcs > 0 && ab + rest > ar.cap) {
             std::snprintf(g_last_error, sizeof(g_last_error),
@@ -3630,7 +3640,8 @@ escg_status step_mcs(const escg_params *p, uint8_t *d_lattice, uint32_t mcs0,
     // one span serves the exchange area or, if the cooperative launch is
     // refused, the ping-pong lattice of the per-MCS launches
     void *span = nullptr;
-    s = ar.take(persistent ? std::max<size_t>(plan.scratch_bytes(), N) : N,
+    s = ar.take(persistent ? std::max<size_t>(plan.scratch_bytes(n_mcs), N)
+                           : N,
                 &span);
     if (s != ESCG_OK)
         return lds_too ? in_lds() : s;

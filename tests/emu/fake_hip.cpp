@@ -24,6 +24,7 @@ bool capturing = false;
 // What a device-to-host copy of `row_words`-word count rows holds: every
 // species alive, but in rows `stop_row` and after of the copy.
 uint32_t row_words = 0, stop_row = ~0u;
+uint64_t allocated = 0; // bytes of all stream-ordered allocations
 dim3 call_grid, call_block;
 size_t call_lds;
 hipStream_t call_stream;
@@ -42,12 +43,14 @@ void fake_reset(uint32_t refuse, uint32_t capture, uint32_t words,
                 uint32_t stop)
 {
     launches.clear();
+    allocated = 0;
     refuse_from = refuse;
     cooperative = 0;
     capturing = capture != 0;
     row_words = words;
     stop_row = stop;
 }
+uint64_t fake_allocated() { return allocated; }
 uint32_t fake_launches() { return (uint32_t)launches.size(); }
 const char *fake_launch(uint32_t i, uint32_t *out)
 {
@@ -122,6 +125,7 @@ hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus *s)
 }
 hipError_t hipMallocAsync(void **p, size_t n, hipStream_t)
 {
+    allocated += n;
     *p = std::calloc(1, n + 256);
     return *p ? hipSuccess : hipErrorOutOfMemory;
 }

@@ -36,6 +36,7 @@ class Fake:
     def __init__(self, so):
         self.dll = C.CDLL(so, mode=C.RTLD_GLOBAL)
         self.dll.fake_launch.restype = C.c_char_p
+        self.dll.fake_allocated.restype = C.c_uint64
         # the binding imports torch only to share its HIP runtime
         sys.modules["torch"] = types.ModuleType("torch")
         from paper_2508_16639_amd import escg

@@ -113,6 +113,24 @@ def test_sides_without_a_tile_plan(fake_so):
     fake_hip.run(fake_so, __file__, "no_tile_plan")
 
 
+def short_patch_runs(f):
+    """A run that ends before its first halo exchange takes no exchange area:
+    its scratch is the L * L bytes of the path without patches."""
+    for L in (402, 512, 700, 1500, 3302):
+        for static in (False, True):
+            f.reset()
+            assert f.step(f.params(L), 1, static=static) == 0
+            assert len(f.names("patch_kernel")) == 1
+            assert f.dll.fake_allocated() == (0 if static else L * L), L
+    f.reset()
+    assert f.step(f.params(700), 40) == 0
+    assert f.dll.fake_allocated() > 700 * 700
+
+
+def test_short_runs_take_no_exchange_area(fake_so):
+    fake_hip.run(fake_so, __file__, "short_patch_runs")
+
+
 if __name__ == "__main__":
     globals()[sys.argv[2]](fake_hip.Fake(sys.argv[1]),
                            *map(int, sys.argv[3:]))
