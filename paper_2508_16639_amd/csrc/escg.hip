@@ -713,7 +713,11 @@ __global__ __launch_bounds__(1024) void tiled_persistent_kernel(TiledArgs a)
 // launch, halos exchanged once per G.K MCS (escg_patch.hpp)
 // ---------------------------------------------------------------------------
 struct PatchArgs {
-    uint8_t *lattice;   // in/out
+    const uint8_t *src; // the lattice as it is
+    uint8_t *lattice;   // receives the result; src itself only if n_mcs > G.K:
+                        // a patch's first exchange waits for its neighbours'
+                        // halos, and so for their loads from src, but without
+                        // one a patch may start when a neighbour has ended
     uint64_t *exch;     // exchange slot 0, slot 1 xstride words on; tags
                         // pre-set (patch_prep_kernel)
     uint32_t *abort;    // 1 word, zeroed
@@ -991,7 +995,7 @@ __global__ __launch_bounds__(1024) void patch_kernel(PatchArgs a)
     if (threadIdx.x == 0)
         TB.misc[0] = 0;
     __syncthreads();
-    patch_load(src, a.lattice, G, P);
+    patch_load(src, a.src, G, P);
     setup_tables(TB, a.dom, a.moore != 0, kProb ? a.ab : nullptr);
     const auto qc = make_quad_ctx<kProb>(TB, a.T1, a.T2); // after a barrier
     uint32_t s = 0;
@@ -1515,10 +1519,12 @@ __global__ __launch_bounds__(kSweepThreads, 4) void patch_sweep_kernel(
 }
 
 // What a patch launch needs set: exchange slot 0 tagged 0, slot 1 tagged 1
-// (neither matches its first use), the abort words and the count rows 0.
+// (neither matches its first use), the abort word and the count rows 0, or, in
+// a run without an exchange (slot_dwords 0, abort null), a copy of the lattice.
 __global__ void patch_prep_kernel(uint32_t *exch, uint32_t slot_dwords,
                                   uint32_t *abort, uint32_t *counts,
-                                  size_t n_counts)
+                                  size_t n_counts, uint32_t *copy,
+                                  const uint32_t *lattice, size_t n_copy)
 {
     const size_t step = (size_t)gridDim.x * blockDim.x;
     const size_t i0 = blockIdx.x * (size_t)blockDim.x + threadIdx.x;
@@ -1527,7 +1533,9 @@ __global__ void patch_prep_kernel(uint32_t *exch, uint32_t slot_dwords,
                                   : exch_tag(1) ^ 0x80808080u;
     for (size_t i = i0; i < n_counts; i += step)
         counts[i] = 0;
-    if (i0 == 0)
+    for (size_t i = i0; i < n_copy; i += step)
+        copy[i] = lattice[i];
+    if (i0 == 0 && abort)
         abort[0] = 0;
 }
 
@@ -2685,36 +2693,41 @@ PatchPlan plan_patch(uint32_t L, uint32_t S)
     return plan;
 }
 
-// Words of an exchange slot of all patches in a run of n_mcs MCS: none where
-// the run ends before its first exchange (allocated anew after a
-// synchronisation, the slots of L = 700 cost a call of one MCS 25 us of 73).
-uint32_t patch_exchange_words(const PatchPlan &plan, uint32_t n_mcs)
-{
-    const PatchGeom &G = plan.G;
-    return n_mcs <= G.K ? 0u : G.PY * G.PX * G.slot_words;
-}
-
-// Scratch of a patch launch: two exchange slots per patch and the abort word.
+// Scratch of a run of n_mcs MCS or less on patches: two exchange slots per
+// patch and the abort word, or, where it ends before its first exchange, a copy
+// of the lattice.
 size_t patch_scratch_bytes(const PatchPlan &plan, uint32_t n_mcs)
 {
-    return 2 * (size_t)patch_exchange_words(plan, n_mcs) * 8 + 256;
+    const PatchGeom &G = plan.G;
+    const size_t N = (size_t)G.L * G.L;
+    return n_mcs <= G.K
+               ? N
+               : std::max(N, 2 * (size_t)G.PY * G.PX * G.slot_words * 8 + 256);
 }
 
 // n_mcs > 0 MCS with the patch kernel; counts: every row, row 0 included.
-// area: patch_scratch_bytes(plan, n_mcs).  As run_tiled_persistent otherwise.
+// area: patch_scratch_bytes(plan, n_mcs).  src: a copy of the lattice, or null.
+// As run_tiled_persistent otherwise, but that a run without an exchange, whose
+// patches wait for nothing, is an ordinary launch that reads a copy of the
+// lattice (src, or made in area).
 escg_status run_patch(const escg_params *p, const Derived &d,
                       const PatchPlan &plan, uint8_t *lattice, uint32_t mcs0,
                       uint32_t n_mcs, uint32_t *counts, hipStream_t st,
-                      uint8_t *area, uint32_t *abort_out = nullptr)
+                      uint8_t *area, const uint8_t *src = nullptr,
+                      uint32_t *abort_out = nullptr)
 {
     const PatchGeom &G = plan.G;
     const uint32_t T = G.PY * G.PX;
+    const bool alone = n_mcs <= G.K;
     PatchArgs a;
     std::memset(&a, 0, sizeof(a));
+    a.src = src ? src : alone ? area : lattice;
     a.lattice = lattice;
-    a.exch = reinterpret_cast<uint64_t *>(area);
-    a.xstride = patch_exchange_words(plan, n_mcs);
-    a.abort = reinterpret_cast<uint32_t *>(a.exch + 2 * (size_t)a.xstride);
+    if (!alone) {
+        a.exch = reinterpret_cast<uint64_t *>(area);
+        a.xstride = T * G.slot_words;
+        a.abort = reinterpret_cast<uint32_t *>(a.exch + 2 * (size_t)a.xstride);
+    }
     a.counts = counts;
     a.seed = p->seed;
     a.G = G;
@@ -2732,16 +2745,26 @@ escg_status run_patch(const escg_params *p, const Derived &d,
     for (int i = 0; i < 32; ++i)
         a.dom[i] = p->dom[i];
     const size_t n_counts = counts ? (size_t)(n_mcs + 1) * (p->S + 1) : 0;
-    const size_t words = std::max<size_t>(4 * (size_t)a.xstride, n_counts);
-    const uint32_t blocks =
-        (uint32_t)std::max<size_t>(1, std::min<size_t>(512, (words + 255) / 256));
-    hipLaunchKernelGGL(patch_prep_kernel, dim3(blocks), dim3(256), 0, st,
-                       reinterpret_cast<uint32_t *>(a.exch), 2 * a.xstride,
-                       a.abort, counts, n_counts);
+    const size_t n_copy = a.src == area ? (size_t)G.L * G.L / 4 : 0;
+    const size_t words =
+        std::max(std::max<size_t>(4 * (size_t)a.xstride, n_counts), n_copy);
+    if (words) {
+        const uint32_t blocks =
+            (uint32_t)std::min<size_t>(512, (words + 255) / 256);
+        hipLaunchKernelGGL(patch_prep_kernel, dim3(blocks), dim3(256), 0, st,
+                           reinterpret_cast<uint32_t *>(a.exch), 2 * a.xstride,
+                           a.abort, counts, n_counts,
+                           reinterpret_cast<uint32_t *>(area),
+                           reinterpret_cast<const uint32_t *>(lattice),
+                           n_copy);
+    }
     void *args[] = {&a};
     const void *fn = patch_kernel_fn(d.small, d.prob, plan.slots);
     allow_dynamic_lds(fn, plan.lds);
     const uint32_t nt = plan.threads + (counts && plan.counter ? 64 : 0);
+    if (alone)
+        return last_hip(hipLaunchKernel(fn, dim3(T), dim3(nt), args, plan.lds,
+                                        st));
     const hipError_t e = hipLaunchCooperativeKernel(
         fn, dim3(T), dim3(nt), args, (unsigned)plan.lds, st);
     if (e != hipSuccess) {
@@ -2978,7 +3001,7 @@ escg_status run_until_persistent(const escg_params *p, const Derived &d,
                        uint32_t *aword) {
         return plan.patch.ok
                    ? run_patch(p, d, plan.patch, lattice, mcs0 + from, n,
-                               rows, st, area, aword)
+                               rows, st, area, saved, aword)
                    : run_tiled_persistent(p, d, plan.tiled, lattice,
                                           mcs0 + from, n, rows, st, area,
                                           aword);

@@ -114,20 +114,30 @@ def test_sides_without_a_tile_plan(fake_so):
 
 
 def short_patch_runs(f):
-    """A run that ends before its first halo exchange takes no exchange area:
-    its scratch is the L * L bytes of the path without patches."""
-    for L in (402, 512, 700, 1500, 3302):
+    """A run on patches that ends before its first halo exchange: patches wait
+    for nothing and may start when a neighbour has ended, so they read a copy
+    of the lattice, in an ordinary launch; the copy is all the scratch."""
+    for L in (90, 402, 512, 700, 1500, 3302):
         for static in (False, True):
-            f.reset()
-            assert f.step(f.params(L), 1, static=static) == 0
-            assert len(f.names("patch_kernel")) == 1
-            assert f.dll.fake_allocated() == (0 if static else L * L), L
-    f.reset()
-    assert f.step(f.params(700), 40) == 0
-    assert f.dll.fake_allocated() > 700 * 700
+            for counts in (False, True):
+                f.reset()
+                assert f.step(f.params(L), 1, counts, static) == 0
+                prep, run = f.launches()
+                assert "patch_prep_kernel" in prep.name
+                assert prep.grid == min(512, (L * L // 4 + 255) // 256)
+                assert "patch_kernel" in run.name and not run.cooperative
+                assert f.dll.fake_allocated() == (0 if static else L * L), L
+        f.reset()
+        assert f.step(f.params(L), 8) == 0
+        assert [x.cooperative for x in f.names("patch_kernel")] == [True]
+        # with a copy of the lattice at hand
+        f.reset(words=4)
+        assert f.until(f.params(512), 1) == 0
+        prep, run = f.names("patch")
+        assert not run.cooperative and prep.grid == 1 # the count rows
 
 
-def test_short_runs_take_no_exchange_area(fake_so):
+def test_runs_without_an_exchange_read_a_copy(fake_so):
     fake_hip.run(fake_so, __file__, "short_patch_runs")
 
 
