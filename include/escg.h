@@ -72,7 +72,8 @@ typedef int32_t escg_status;
  * whole lattice in one workgroup's LDS; tiled launches (of up to three MCS
  * each where the library decides, of one where the caller names the route, a
  * tile shape or a workgroup size); the
- * persistent kernels (all MCS in one cooperative launch, every part of the
+ * persistent kernels (all MCS in one launch, cooperative if its workgroups
+ * wait for each other, every part of the
  * lattice resident in LDS: uneven patches with deep halos, or equal tiles
  * where the launch choices name a tile shape or a workgroup size, or the
  * patches would be too large). */

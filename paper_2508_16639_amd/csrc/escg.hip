@@ -2576,7 +2576,9 @@ uint32_t list_simd_load(uint32_t nq, uint32_t nt)
     return std::max(std::max(simd[0], simd[1]), std::max(simd[2], simd[3]));
 }
 
-PatchPlan plan_patch_uncached(uint32_t L, uint32_t S)
+// one > 0: the lattice as a single patch with a halo for `one` MCS, at most two
+// quads a thread.
+PatchPlan plan_patch_uncached(uint32_t L, uint32_t S, uint32_t one)
 {
     PatchPlan best;
     const DeviceInfo di = device_info();
@@ -2588,22 +2590,23 @@ PatchPlan plan_patch_uncached(uint32_t L, uint32_t S)
     PatchGeom G{};
     G.L = L;
     const uint32_t Lb = G.Lb(), Q = G.Q(), part = G.part();
-    for (uint32_t K = 1; K <= 7; ++K) {
+    const uint32_t most = one ? 1u : cus; // patches
+    for (uint32_t K = one ? one : 1u; K <= (one ? one : 7u); ++K) {
         G.K = K;
         G.HQ = (4 * K + 1 + 7) / 8;
-        for (uint32_t PX = 1; PX <= std::min(Q, cus); ++PX) {
+        for (uint32_t PX = 1; PX <= std::min(Q, most); ++PX) {
             // strips come from the next patch alone, and the partial quad
             // keeps out of every halo
             const uint32_t tq = Q / PX, TQ = (Q + PX - 1) / PX;
             if (tq < G.HQ || (part && tq < 2 * G.HQ + 1))
                 continue;
-            for (uint32_t PY = 1; PY <= std::min(Lb, cus / PX); ++PY) {
+            for (uint32_t PY = 1; PY <= std::min(Lb, most / PX); ++PY) {
                 const uint32_t th = 2 * (Lb / PY);
                 const uint32_t TH = 2 * ((Lb + PY - 1) / PY);
                 if (th < G.HR())
                     continue;
                 const uint32_t nq = (TH / 2 + G.HR()) * (TQ + 2 * G.HQ);
-                if (nq > 1024 * kPatchSlots)
+                if (nq > 1024 * (one ? 2 : kPatchSlots))
                     continue;
                 // one quad per thread, or the workgroup size with the least
                 // load of the busiest SIMD (ties: more waves)
@@ -2674,20 +2677,20 @@ PatchPlan plan_patch_uncached(uint32_t L, uint32_t S)
     return best;
 }
 
-PatchPlan plan_patch(uint32_t L, uint32_t S)
+PatchPlan plan_patch(uint32_t L, uint32_t S, uint32_t one = 0)
 {
     static std::mutex mu;
-    static std::map<std::tuple<int, uint32_t, bool>, PatchPlan> cache;
+    static std::map<std::tuple<int, uint32_t, bool, uint32_t>, PatchPlan> cache;
     int dev = 0;
     (void)hipGetDevice(&dev);
-    const auto key = std::make_tuple(dev, L, S <= 7);
+    const auto key = std::make_tuple(dev, L, S <= 7, one);
     {
         std::lock_guard<std::mutex> lk(mu);
         auto it = cache.find(key);
         if (it != cache.end())
             return it->second;
     }
-    const PatchPlan plan = plan_patch_uncached(L, S <= 7 ? 7u : 31u);
+    const PatchPlan plan = plan_patch_uncached(L, S <= 7 ? 7u : 31u, one);
     std::lock_guard<std::mutex> lk(mu);
     cache[key] = plan;
     return plan;
@@ -2695,14 +2698,15 @@ PatchPlan plan_patch(uint32_t L, uint32_t S)
 
 // Scratch of a run of n_mcs MCS or less on patches: two exchange slots per
 // patch and the abort word, or, where it ends before its first exchange, a copy
-// of the lattice.
+// of the lattice (a single patch needs none: it loads all before it stores).
+// At least the L * L bytes of the path that takes a refused launch's place.
 size_t patch_scratch_bytes(const PatchPlan &plan, uint32_t n_mcs)
 {
     const PatchGeom &G = plan.G;
-    const size_t N = (size_t)G.L * G.L;
-    return n_mcs <= G.K
-               ? N
-               : std::max(N, 2 * (size_t)G.PY * G.PX * G.slot_words * 8 + 256);
+    const size_t N = (size_t)G.L * G.L, T = (size_t)G.PY * G.PX;
+    if (n_mcs <= G.K)
+        return T == 1 ? 0 : N;
+    return std::max(N, 2 * T * G.slot_words * 8 + 256);
 }
 
 // n_mcs > 0 MCS with the patch kernel; counts: every row, row 0 included.
@@ -2721,7 +2725,7 @@ escg_status run_patch(const escg_params *p, const Derived &d,
     const bool alone = n_mcs <= G.K;
     PatchArgs a;
     std::memset(&a, 0, sizeof(a));
-    a.src = src ? src : alone ? area : lattice;
+    a.src = src ? src : alone && T > 1 ? area : lattice;
     a.lattice = lattice;
     if (!alone) {
         a.exch = reinterpret_cast<uint64_t *>(area);
@@ -2745,7 +2749,8 @@ escg_status run_patch(const escg_params *p, const Derived &d,
     for (int i = 0; i < 32; ++i)
         a.dom[i] = p->dom[i];
     const size_t n_counts = counts ? (size_t)(n_mcs + 1) * (p->S + 1) : 0;
-    const size_t n_copy = a.src == area ? (size_t)G.L * G.L / 4 : 0;
+    const size_t n_copy =
+        a.src == area && !src && alone && T > 1 ? (size_t)G.L * G.L / 4 : 0;
     const size_t words =
         std::max(std::max<size_t>(4 * (size_t)a.xstride, n_counts), n_copy);
     if (words) {
@@ -2920,16 +2925,29 @@ struct ResidentPlan {
     size_t scratch_bytes(uint32_t n_mcs) const // of a run of n_mcs MCS or less
     {
         return patch.ok ? patch_scratch_bytes(patch, n_mcs)
-                        : exchange_bytes(tiled);
+                        : std::max(exchange_bytes(tiled),
+                                   (size_t)tiled.G.L * tiled.G.L);
     }
 };
 
-ResidentPlan plan_resident(const escg_params *p)
+// n_mcs: MCS of the run, 0 if not known.
+//
+// A single patch for a few MCS of a small lattice with L % 8 != 0: one ordinary
+// launch (and one for the count rows) that needs no scratch, where patches on
+// many CUs need a copy of the lattice or a cooperative launch.  us of a call
+// with counts, many / one (in place in one LDS, the path before patches): L =
+// 90, 1 MCS 35 / 24 (25), 4 MCS 54 / 36 (47); L = 130, 1 MCS 35 / 29 (24), 4
+// MCS 54 / 46 (50); past two quads a thread one CU takes longer than that.
+ResidentPlan plan_resident(const escg_params *p, uint32_t n_mcs = 0)
 {
     ResidentPlan r;
     const escg_launch &ln = p->launch;
-    if (ln.tile_h == 0 && ln.threads == 0)
-        r.patch = plan_patch(p->L, p->S);
+    if (ln.tile_h == 0 && ln.threads == 0) {
+        if ((p->L & 7u) != 0 && p->L > kWholeMaxL && n_mcs >= 1 && n_mcs <= 4)
+            r.patch = plan_patch(p->L, p->S, n_mcs);
+        if (!r.patch.ok)
+            r.patch = plan_patch(p->L, p->S);
+    }
     if (!r.patch.ok && (p->L & 7u) == 0)
         r.tiled = plan_tiled(p->L, p->S, plan_hints(p));
     return r;
@@ -3614,16 +3632,14 @@ escg_status step_mcs(const escg_params *p, uint8_t *d_lattice, uint32_t mcs0,
     if (r == Route::kUnsupported)
         return ESCG_EUNSUPPORTED;
     const bool persistent = r == Route::kPersistent;
-    const ResidentPlan plan = persistent ? plan_resident(p) : ResidentPlan{};
+    const ResidentPlan plan =
+        persistent ? plan_resident(p, n_mcs) : ResidentPlan{};
     if (ar.base) {
         const size_t ab = d.prob ? Arena::round(d.ab.size() * 4) : 0;
         const size_t rest =
-            r == Route::kLds ? 0
-                             : Arena::round(persistent
-                                                ? std::max<size_t>(
-                                                      plan.scratch_bytes(n_mcs),
-                                                      N)
-                                                : N);
+            r == Route::kLds
+                ? 0
+                : Arena::round(persistent ? plan.scratch_bytes(n_mcs) : N);
         if (n_mcs > 0 && ab + rest > ar.cap) {
             std::snprintf(g_last_error, sizeof(g_last_error),
                           "needs %zu bytes of static scratch, %zu available",
@@ -3663,9 +3679,9 @@ escg_status step_mcs(const escg_params *p, uint8_t *d_lattice, uint32_t mcs0,
     // one span serves the exchange area or, if the cooperative launch is
     // refused, the ping-pong lattice of the per-MCS launches
     void *span = nullptr;
-    s = ar.take(persistent ? std::max<size_t>(plan.scratch_bytes(n_mcs), N)
-                           : N,
-                &span);
+    const size_t span_bytes = persistent ? plan.scratch_bytes(n_mcs) : N;
+    if (span_bytes)
+        s = ar.take(span_bytes, &span);
     if (s != ESCG_OK)
         return lds_too ? in_lds() : s;
     if (persistent) {

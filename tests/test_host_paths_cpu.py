@@ -117,7 +117,7 @@ def short_patch_runs(f):
     """A run on patches that ends before its first halo exchange: patches wait
     for nothing and may start when a neighbour has ended, so they read a copy
     of the lattice, in an ordinary launch; the copy is all the scratch."""
-    for L in (90, 402, 512, 700, 1500, 3302):
+    for L in (96, 250, 402, 512, 700, 1500, 3302):
         for static in (False, True):
             for counts in (False, True):
                 f.reset()
@@ -139,6 +139,30 @@ def short_patch_runs(f):
 
 def test_runs_without_an_exchange_read_a_copy(fake_so):
     fake_hip.run(fake_so, __file__, "short_patch_runs")
+
+
+def single_patches(f):
+    """A few MCS of a small lattice with L % 8 != 0: one ordinary launch of one
+    workgroup, no scratch, and one launch more for count rows."""
+    for L, S, most in ((90, 3, 4), (122, 9, 4), (138, 3, 4), (154, 3, 2),
+                       (162, 31, 1), (170, 3, 0), (96, 3, 0), (398, 3, 0)):
+        for n in range(1, 7):
+            for static in (False, True):
+                f.reset()
+                assert f.step(f.params(L, S=S), n, True, static) == 0
+                prep, run = f.names("patch")
+                one = n <= most
+                assert (run.grid == 1) == one, (L, n, run)
+                assert not one or not run.cooperative
+                assert not one or f.dll.fake_allocated() == 0
+                assert f.escg.last_route() == "persistent"
+            f.reset()
+            assert f.step(f.params(L, S=S), n, False) == 0
+            assert not one or len(f.launches()) == 1
+
+
+def test_a_few_mcs_on_a_single_patch(fake_so):
+    fake_hip.run(fake_so, __file__, "single_patches")
 
 
 if __name__ == "__main__":

@@ -7,7 +7,7 @@ import pytest
 import oracle as O
 from paper_2508_16639_amd import escg
 from paper_2508_16639_amd.workloads import random_lattice
-from tests.gpu_util import dev, host, pair
+from tests.gpu_util import dev, host, pair, probabilities
 
 pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
@@ -39,6 +39,32 @@ def test_short_steps_beside_a_batch(L, n):
     O.o2_run(j, g, 0, rounds * n, want_counts=False)
     for lat in lats:
         assert np.array_equal(host(lat), g)
+
+
+@pytest.mark.parametrize("L,S,n,moore,prob", [
+    (90, 3, 1, False, False), (90, 5, 4, True, False), (94, 13, 2, False, True),
+    (100, 3, 3, False, False), (122, 31, 4, True, False),
+    (130, 7, 4, False, True), (138, 3, 4, False, False),
+    (154, 3, 2, True, False), (162, 8, 1, False, True)])
+def test_single_patch_bit_exact(L, S, n, moore, prob):
+    """A few MCS of a small lattice with L % 8 != 0: one patch, one and two
+    quads a thread, in place."""
+    D = O.circulant_matrix(S, [1, 3] if S > 4 else [1])
+    P = probabilities(D, seed=L) if prob else None
+    p, j = pair(L, S, None, 2.0, seed=L + 5, replica=2, D=D, moore=moore, P=P)
+    g0 = random_lattice(L, S, seed=L, domain=3)
+    ref = g0.copy()
+    rc = O.o2_run(j, ref, 1 << 20, n)
+    for fn in (escg.step_mcs, escg.step_mcs_static):
+        for counts in (True, False):
+            lat = dev(g0)
+            cnt = torch.full(((n + 1) * (S + 1),), -1, dtype=torch.int32,
+                             device="cuda:0") if counts else None
+            fn(p, lat, 1 << 20, n, cnt)
+            assert escg.last_route() == "persistent"
+            assert np.array_equal(host(lat), ref), counts
+            if counts:
+                assert np.array_equal(host(cnt).reshape(rc.shape), rc)
 
 
 def test_run_until_of_a_few_mcs():
