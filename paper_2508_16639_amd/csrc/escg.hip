@@ -1162,8 +1162,8 @@ __global__ __launch_bounds__(kWholeThreads) void whole_kernel(JobDev J,
 }
 
 // ---------------------------------------------------------------------------
-// Lattices of which a CU's LDS holds two copies (L <= 276 for S <= 7), one
-// 1024-thread workgroup per job and CU, several quads a thread
+// Lattices of which a CU's LDS holds two copies (L <= 280, or 264 for S > 7),
+// one workgroup of up to 1024 threads per job and CU, several quads a thread
 // ---------------------------------------------------------------------------
 // Bound by vector issue and, below some 1000 quads, by the four barriers of
 // an MCS.  Against two 512-thread workgroups a CU that update one copy in
@@ -1317,7 +1317,7 @@ __device__ __forceinline__ void run_job_pair(const JobDev &J, uint8_t *base, uin
         case 2: run(std::integral_constant<int, 2>()); break;
         case 3: run(std::integral_constant<int, 3>()); break;
         case 4: run(std::integral_constant<int, 4>()); break;
-        default: run(std::integral_constant<int, 5>()); break;
+        default: run(std::integral_constant<int, kWholeSlots>()); break;
         }
     store();
     if (J.result) {
@@ -2110,11 +2110,13 @@ const void *persistent_kernel(bool packed, bool prob, bool list)
 escg_status launch_whole(const JobDev &J, bool small, uint8_t *base,
                          hipStream_t st);
 
-// Two copies of a lattice of lds_job_bytes `bytes` beside the tables of S.
-bool pair_fits(size_t bytes, uint32_t S)
+// Two copies of a lattice of lds_job_bytes `bytes` beside the tables of S, and
+// no more quads (q) than its kernels give a workgroup's threads.
+bool pair_fits(size_t bytes, uint32_t q, uint32_t S)
 {
     const DeviceInfo di = device_info();
-    return 2 * bytes + static_lds_bytes(S) + 64 <=
+    return q <= kWholeSlots * kPairThreads &&
+           2 * bytes + static_lds_bytes(S) + 64 <=
            (di.lds_max ? di.lds_max : 65536);
 }
 
@@ -2126,7 +2128,8 @@ escg_status launch_lds_single(const JobDev &J, bool small, uint8_t *base,
     // without count rows two copies do, the stop condition tested now and
     // then (L = 100: 9.9 -> 2.6 us per MCS, L = 250: 33 -> 11)
     const bool pair =
-        !J.counts && pair_fits(lds_job_bytes(J.L, J.S), J.S);
+        !J.counts &&
+        pair_fits(lds_job_bytes(J.L, J.S), whole_quads(J.L), J.S);
     const size_t lds = (pair ? 2 : 1) * lds_job_bytes(J.L, J.S);
     const uint32_t nt = pair ? kPairThreads : lds_threads(J.L);
     const void *fn =
@@ -4219,7 +4222,8 @@ escg_status escg_batch_run(uint32_t n, const escg_params *h_params,
     // L % 8 != 0 a third slower in place) say
     const uint32_t cus = (uint32_t)std::max(1, device_info().cus);
     bool pair = !ln.threads && !ln.wg_per_cu &&
-                pair_fits(lds_need, all_small ? 7u : ESCG_MAX_SPECIES);
+                pair_fits(lds_need, whole_quads(Lmax),
+                          all_small ? 7u : ESCG_MAX_SPECIES);
     if (pair && n > cus && (ln.max_wgs == 0 || ln.max_wgs > cus)) {
         double in_place = 0, two_copies = 0;
         for (uint32_t j = 0; j < n; ++j) {

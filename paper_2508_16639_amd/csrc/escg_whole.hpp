@@ -112,7 +112,7 @@ __device__ __forceinline__ void whole_pass(const uint8_t *src, uint8_t *dst,
 // Several quads a thread (larger lattices, two copies): quad tid + i *
 // threads in row-major order, i < kSlots = ceil(quads / threads).  Threads
 // past the last quad repeat it; a wave with no quad in the last slot skips it.
-constexpr uint32_t kWholeSlots = 5;
+constexpr int kWholeSlots = 5; // at most (L = 280 has 4900 quads)
 
 template <int kSlots>
 struct WholeSlots {

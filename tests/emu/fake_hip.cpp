@@ -21,6 +21,7 @@ std::map<const void *, size_t> variables;
 uint32_t refuse_from = ~0u; // cooperative launches from this one on fail
 uint32_t cooperative = 0;
 bool capturing = false;
+size_t lds_bytes = 160 * 1024; // of a CU
 // What a device-to-host copy of `row_words`-word count rows holds: every
 // species alive, but in rows `stop_row` and after of the copy.
 uint32_t row_words = 0, stop_row = ~0u;
@@ -39,6 +40,7 @@ hipError_t record(const void *f, dim3 g, dim3 b, size_t lds, bool coop)
 
 extern "C" {
 // ---- for the tests
+void fake_lds(uint32_t bytes) { lds_bytes = bytes; } // before any other call
 void fake_reset(uint32_t refuse, uint32_t capture, uint32_t words,
                 uint32_t stop)
 {
@@ -106,7 +108,7 @@ hipError_t hipGetDeviceProperties(hipDeviceProp_t *p, int)
 {
     std::memset(p, 0, sizeof(*p));
     p->multiProcessorCount = 256;
-    p->sharedMemPerBlock = 160 * 1024;
+    p->sharedMemPerBlock = lds_bytes;
     return hipSuccess;
 }
 hipError_t hipFuncSetAttribute(const void *, hipFuncAttribute, int)
@@ -168,7 +170,7 @@ hipError_t hipOccupancyMaxActiveBlocksPerMultiprocessor(int *n, const void *,
                                                         int block, size_t lds)
 {
     // the kernels' registers: four waves a SIMD
-    *n = (int)std::min<size_t>(1024 / block, 160 * 1024 / (lds + 2048));
+    *n = (int)std::min<size_t>(1024 / block, lds_bytes / (lds + 2048));
     return hipSuccess;
 }
 hipError_t hipLaunchKernel(const void *f, dim3 g, dim3 b, void **, size_t lds,

@@ -78,6 +78,17 @@ class Fake:
         return self.lib.escg_run_until_extinction(
             C.byref(p.c()), lat.ctypes.data, 0, n, mode, res.ctypes.data, None)
 
+    def batch(self, ps, ns, mode=0):
+        n = len(ps)
+        offs = np.cumsum([0] + [p.L * p.L for p in ps]).astype(np.uint64)
+        buf = np.zeros(int(offs[-1]), np.uint8)
+        res = np.zeros(n * self.escg.BATCH_RESULT_WORDS, np.uint32)
+        cps = (self.escg.CParams * n)(*[p.c() for p in ps])
+        return self.lib.escg_batch_run(
+            n, cps, offs.ctypes.data_as(C.POINTER(C.c_uint64)),
+            buf.ctypes.data, None, (C.c_uint32 * n)(*ns), mode, 1,
+            res.ctypes.data, None)
+
     def step_batch(self, ps, ns):
         n = len(ps)
         lats = [np.zeros(p.L * p.L, np.uint8) for p in ps]

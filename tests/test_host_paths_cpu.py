@@ -165,6 +165,29 @@ def test_a_few_mcs_on_a_single_patch(fake_so):
     fake_hip.run(fake_so, __file__, "single_patches")
 
 
+def pair_limits(f, lds):
+    """The kernel with two copies of a lattice is taken only up to the quads
+    that it gives its threads, and the LDS."""
+    f.dll.fake_lds(lds)
+    for L, S, pair in ((90, 3, True), (276, 3, True), (278, 3, True),
+                       (280, 3, True), (282, 3, lds > 160 * 1024),
+                       (284, 3, lds > 160 * 1024), (288, 3, False),
+                       (300, 3, False), (90, 9, True), (264, 9, True),
+                       (266, 9, lds > 160 * 1024), (300, 9, False)):
+        p = f.params(L, S=S, route="lds")
+        f.reset(words=S + 1)
+        assert f.until(p, 9) == 0
+        assert bool(f.names("pair_single_kernel")) == pair, (L, S)
+        f.reset()
+        assert f.batch([p], [9]) == 0
+        assert bool(f.names("pair_batch_kernel")) == pair, (L, S)
+
+
+@pytest.mark.parametrize("lds", [160 * 1024, 400 * 1024])
+def test_limits_of_the_two_copy_kernel(fake_so, lds):
+    fake_hip.run(fake_so, __file__, "pair_limits", lds)
+
+
 if __name__ == "__main__":
     globals()[sys.argv[2]](fake_hip.Fake(sys.argv[1]),
                            *map(int, sys.argv[3:]))
