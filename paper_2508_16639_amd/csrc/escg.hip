@@ -16,7 +16,9 @@
 //                      condition tested in windows of MCS (no count rows)
 //   patch_kernel       one lattice of any even side in uneven patches, one
 //                      per CU and resident for all MCS of a call, with a halo
-//                      deep enough for several MCS between exchanges
+//                      deep enough for several MCS between exchanges (calls
+//                      that end before the first one: no waits, an ordinary
+//                      launch that reads a copy of the lattice)
 //   tiled_persistent_* the same with equal tiles and an exchange every MCS:
 //                      tile shapes asked for, lattices past the patch
 //                      kernel's three quads a thread, several jobs a launch
@@ -709,7 +711,7 @@ __global__ __launch_bounds__(1024) void tiled_persistent_kernel(TiledArgs a)
 }
 
 // ---------------------------------------------------------------------------
-// Patch kernel: all MCS of a lattice of any even side in one cooperative
+// Patch kernel: all MCS of a lattice of any even side in one
 // launch, halos exchanged once per G.K MCS (escg_patch.hpp)
 // ---------------------------------------------------------------------------
 struct PatchArgs {
@@ -1175,35 +1177,47 @@ __global__ __launch_bounds__(kWholeThreads) void whole_kernel(JobDev J,
 constexpr uint32_t kPairThreads = 1024;
 
 // The stop condition of the state in `src` (nw words), by the species that are
-// there, not by their counts: a wave reads words until it has seen enough of
-// them, one read almost always, so a test costs little more than its barrier
-// (counting the sites took as long as an MCS at L = 64).  seen: two LDS words,
-// zeroed before the first test; k: 0 and 1 in turn.
+// there, not by their counts (counting the sites took as long as an MCS at L =
+// 64).  Every wave looks at the same 64 words first, spread over the lattice:
+// almost always they hold enough species, and all waves know it without a
+// barrier.  Else they read on together.  seen: two LDS words, zeroed before the
+// first test; k: which of them the next such reading takes.  (The words lie an
+// odd number apart: 32 words apart, at L = 128, they are on two banks and a test
+// took 0.5 us.)
+template <bool kSmall>
 __device__ __forceinline__ bool pair_stop(const uint8_t *src, uint32_t nw,
                                           uint32_t S, uint32_t mode,
-                                          uint32_t *seen, uint32_t k)
+                                          uint32_t *seen, uint32_t &k)
 {
     const uint32_t all = (2u << S) - 2u;
-    const auto goes_on = [&](uint32_t m) {
+    const uint32_t need = mode == ESCG_STOP_FIRST_EXTINCTION ? all : 0u;
+    const auto goes_on = [&](uint32_t m) { // all species, or two of them
         m &= all;
-        return mode == ESCG_STOP_FIRST_EXTINCTION ? m == all
-                                                  : (m & (m - 1u)) != 0;
+        return need ? m == need : (m & (m - 1u)) != 0;
     };
+    const uint32_t sample =
+        min((threadIdx.x & 63u) * (nw >> 6 | 1u), nw - 1u);
+    if (goes_on(species_fold<kSmall>(wave_or(species_bits<kSmall>(
+            *reinterpret_cast<const uint2 *>(src + 8 * sample))))))
+        return false;
     uint32_t m = 0;
     for (uint32_t i = threadIdx.x; (i & ~63u) < nw; i += blockDim.x) {
         uint32_t b = 0;
         if (i < nw)
-            b = species_bits(*reinterpret_cast<const uint2 *>(src + 8 * i));
-        m |= wave_or(b);
+            b = species_bits<kSmall>(
+                *reinterpret_cast<const uint2 *>(src + 8 * i));
+        m |= species_fold<kSmall>(wave_or(b));
         if (goes_on(m))
             break;
     }
     if ((threadIdx.x & 63u) == 0)
         atomicOr(seen + k, m);
     __syncthreads();
-    if (threadIdx.x == 0) // between this test's barrier and the next test
-        seen[k ^ 1u] = 0;
-    return !goes_on(__builtin_amdgcn_readfirstlane(seen[k]));
+    const bool stop = !goes_on(__builtin_amdgcn_readfirstlane(seen[k]));
+    k ^= 1u;
+    if (threadIdx.x == 0) // an MCS's barriers before the next test
+        seen[k] = 0;
+    return stop;
 }
 
 template <bool kPacked, bool kProb>
@@ -1247,10 +1261,11 @@ __device__ __forceinline__ void run_job_pair(const JobDev &J, uint8_t *base, uin
     const auto qc = make_quad_ctx<kProb>(TB, J.T1, J.T2); // after a barrier
 
     const uint32_t replica = J.replica, mcs0 = J.mcs0, mode = J.mode;
-    uint32_t tests = 0;
+    const uint32_t max_mcs = J.max_mcs;
+    uint32_t seen = 0;
     const auto test = [&]() __attribute__((always_inline)) {
         return mode != ESCG_STOP_NONE &&
-               pair_stop(src, nw, S, mode, TB.cnt + 62, tests++ & 1u);
+               pair_stop<kPacked>(src, nw, S, mode, TB.cnt + 62, seen);
     };
     bool stop = test();
     bool replay = false; // the MCS since the last test, one at a time
@@ -1267,11 +1282,11 @@ __device__ __forceinline__ void run_job_pair(const JobDev &J, uint8_t *base, uin
             sf = quad_sel(rf, qc);
         };
         start();
-        while (t < J.max_mcs) {
-            const uint32_t n = min(mode == ESCG_STOP_NONE ? J.max_mcs
+        while (t < max_mcs) {
+            const uint32_t n = min(mode == ESCG_STOP_NONE ? max_mcs
                                    : replay               ? 1u
                                                           : pair_window(t),
-                                   J.max_mcs - t);
+                                   max_mcs - t);
 #pragma unroll 1
             for (uint32_t m = 0; m < n; ++m, ++t) {
                 if ((t & 63u) == 0)
@@ -1306,7 +1321,7 @@ __device__ __forceinline__ void run_job_pair(const JobDev &J, uint8_t *base, uin
                 s = 0;
                 start();
                 __syncthreads();
-            } else if (!replay && t < J.max_mcs && pair_window(t) > 1) {
+            } else if (!replay && t < max_mcs && pair_window(t) > 1) {
                 store();
             }
         }
@@ -1521,6 +1536,7 @@ __global__ __launch_bounds__(kSweepThreads, 4) void patch_sweep_kernel(
 // What a patch launch needs set: exchange slot 0 tagged 0, slot 1 tagged 1
 // (neither matches its first use), the abort word and the count rows 0, or, in
 // a run without an exchange (slot_dwords 0, abort null), a copy of the lattice.
+// (Multi-job launches: the slots of all jobs, their abort words as counts.)
 __global__ void patch_prep_kernel(uint32_t *exch, uint32_t slot_dwords,
                                   uint32_t *abort, uint32_t *counts,
                                   size_t n_counts, uint32_t *copy,
@@ -2264,8 +2280,12 @@ uint32_t tiled_threads(const TileGeom &G, uint32_t cap)
     return nt;
 }
 
-// Automatic routing sends a single job to the persistent path from this side
-// on.
+// Automatic routing sends a single job with L % 8 == 0 to the persistent path
+// from this side on.  us of a step with counts on patches / in one LDS
+// (whole_kernel), S = 3: L = 72, 1 MCS 43 / 15, 200 MCS 386 / 385, 2000 MCS
+// 3446 / 3709; L = 88, 1 MCS 36 / 15, 200 MCS 386 / 409, 2000 MCS 3429 / 3963;
+// S = 8, 200 MCS, L = 72 425 / 516: level at 200 MCS, the patches ahead
+// from there on and the fewer MCS the further behind.
 constexpr uint32_t kPersistentMinL = 72;
 
 
@@ -2794,9 +2814,9 @@ escg_status run_patch(const escg_params *p, const Derived &d,
 // Patches of at most kPatchSlots quads a thread for kSweepThreads threads, two
 // regions of two copies each in a CU's LDS, any number of patches.  More MCS a
 // launch mean fewer loads and stores and a wider halo: 16384^2, 12 MCS, us
-// per MCS with K = 1, 2, 3: 374, 356, 344 (three MCS need one more halo quad a
-// side than two); 4102^2: 44, 36, 43 (the halo costs another round of
-// patches).
+// per MCS with K = 1, 2, 3: 374, 356, 344 (two and three MCS take a halo of two
+// quads a side, one MCS of one); 4102^2: 44, 36, 43 (the halo costs another
+// round of patches).
 PatchPlan plan_sweep_uncached(uint32_t L, uint32_t S, uint32_t n_mcs)
 {
     PatchPlan best;
@@ -3352,10 +3372,11 @@ escg_status launch_multi(std::vector<uint32_t> idx,
                     : nullptr;
     }
     // slot 0 tagged 0, slot 1 tagged 1: neither matches its first use
-    launch_fill(slot0, slot_bytes / 4, exch_tag(2) ^ 0x80808080u, st);
-    launch_fill(slot0 + slot_bytes / 4, slot_bytes / 4,
-                exch_tag(1) ^ 0x80808080u, st);
-    launch_fill(abort0, 16 * (size_t)m, 0, st);
+    const uint32_t blocks = (uint32_t)std::max<size_t>(
+        1, std::min<size_t>(512, (slot_bytes / 2 + 255) / 256));
+    hipLaunchKernelGGL(patch_prep_kernel, dim3(blocks), dim3(256), 0, st,
+                       slot0, (uint32_t)(slot_bytes / 4), nullptr, abort0,
+                       16 * (size_t)m, nullptr, nullptr, (size_t)0);
     escg_status s = ESCG_OK;
     if (hipMemcpyAsync(dev, tbl.data(), sizeof(TiledArgs) * m,
                        hipMemcpyHostToDevice, st) != hipSuccess ||
@@ -4219,7 +4240,12 @@ escg_status escg_batch_run(uint32_t n, const escg_params *h_params,
     // workgroups per CU: the first where every job can have a CU of its own
     // (or the caller allows no more workgroups), else whichever the measured
     // us per MCS and job (see run_job_pair; q quads, other sides of
-    // L % 8 != 0 a third slower in place) say
+    // L % 8 != 0 a third slower in place) say.  The rates are those of S = 3;
+    // other classes only move the line towards two copies: 512 jobs of 300
+    // MCS, us per MCS for two jobs a CU, two copies / in place: L = 160, S = 3
+    // 8.2 / 9.0, with probabilities 11.7 / 12.1, S = 8 8.8 / 16.3; L = 256 13.5
+    // / 14.9, 19.9 / 20.6, 13.9 / 37.0, S = 7 with probabilities 19.9 / 21.5
+    // (at L = 96, left in place, 6.4 / 6.9, 8.5 / 9.0, S = 8 6.7 / 10.5).
     const uint32_t cus = (uint32_t)std::max(1, device_info().cus);
     bool pair = !ln.threads && !ln.wg_per_cu &&
                 pair_fits(lds_need, whole_quads(Lmax),

@@ -329,16 +329,6 @@ __device__ __forceinline__ uint32_t wave_or(uint32_t v)
     return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
 }
 
-// Bits of the values (below 32) of a word's eight bytes.
-__device__ __forceinline__ uint32_t species_bits(uint2 v)
-{
-    uint32_t b = 0;
-#pragma unroll
-    for (uint32_t k = 0; k < 4; ++k)
-        b |= 1u << ((v.x >> (8 * k)) & 31u) | 1u << ((v.y >> (8 * k)) & 31u);
-    return b;
-}
-
 // Species counting for values 0..7 (densities_kernel): v_perm with the byte
 // table {1, 2, 4, ..., 128} maps every byte of a dword to its one-hot code
 // (bytes 12, used as padding, map to 0), so the count of species s in the
@@ -349,6 +339,25 @@ constexpr uint32_t kOneHotHi = 0x80402010u; // table bytes 4..7
 __device__ __forceinline__ uint32_t one_hot_bytes(uint32_t v)
 {
     return __builtin_amdgcn_perm(kOneHotHi, kOneHotLo, v);
+}
+
+// The values in a word's eight bytes, as bits: kSmall (all below 8) the bits of
+// four bytes each, to be or'ed (species_fold); else (below 32) one dword's.
+template <bool kSmall>
+__device__ __forceinline__ uint32_t species_bits(uint2 v)
+{
+    if constexpr (kSmall)
+        return one_hot_bytes(v.x) | one_hot_bytes(v.y);
+    uint32_t b = 0;
+#pragma unroll
+    for (uint32_t k = 0; k < 4; ++k)
+        b |= 1u << ((v.x >> (8 * k)) & 31u) | 1u << ((v.y >> (8 * k)) & 31u);
+    return b;
+}
+template <bool kSmall>
+__host__ __device__ inline uint32_t species_fold(uint32_t b)
+{
+    return kSmall ? (b | b >> 8 | b >> 16 | b >> 24) & 0xFFu : b;
 }
 
 } // namespace escg

@@ -29,7 +29,7 @@ namespace escg {
 // Per-job constants of the quad update (all uniform).  kProb: the job has
 // dominance probabilities; a selection then looks up the pair's thresholds
 // A, B (one LDS table of Sp*Sp pairs of u32, one 8-byte read: with a table
-// each, S = 8 with probabilities took 3.4 instead of 3.2 us per MCS at L = 400
+// each, S = 8 with probabilities took 3.05 instead of 2.86 us per MCS at L = 400
 // and 15.2 instead of 13.0 at L = 3200, S = 5 the same) and compares v = u - T1 with them:
 // v < A the selected cell wins, else v < B the neighbour wins, else nothing.
 // Those three outcomes are rule tables 3, 4, 5.

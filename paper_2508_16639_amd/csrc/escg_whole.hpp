@@ -229,15 +229,16 @@ __device__ __forceinline__ void whole_pass_slots(
 // species that is extinct stays extinct, so a condition that holds at a test
 // has held since some MCS after the last test: the job goes back to the state
 // of that test (kept in its lattice's place in global memory) and tests after
-// every MCS.  So a stop at t costs at most t / 16 MCS run twice and as many
-// past it.  Up to t = 128 every MCS is tested and no state is kept: the test
-// costs little (pair_stop), the copy of the state half an MCS at L = 256.
+// every MCS.  Up to t = 128 every MCS is tested and no state is kept: a test
+// takes 0.3 to 0.5 us of an MCS's 2 to 10 (pair_stop), the copy of the state
+// 2.8 at L = 206.  So a stop up to 128 costs no MCS more, one past it at most an
+// eighth.
 // Batches that stop after 25 MCS (64 of L = 256, 512 of L = 192, 16 of L = 8),
 // us: first test after 32 MCS 1048, 3177, 349; in-place kernel, which tests
-// after every MCS, 789, 2447, 223; now 652, 2517, 207.
+// after every MCS, 789, 2447, 223; now 631, 2445, 192.
 __host__ __device__ inline uint32_t pair_window(uint32_t t)
 {
-    return t < 128u ? 1u : min(32u, t / 16u);
+    return t < 128u ? 1u : min(32u, t / 8u);
 }
 
 // Loads the lattice (shift 0) into `buf`, which holds zeros.

@@ -58,7 +58,7 @@ static int run_case(uint32_t L, uint32_t S, bool moore, const double *r, uint32_
   std::vector<uint32_t> rc((n + 1) * (S + 1));
   orc_o2_run(L, S, D.data(), r[0], r[1], r[2], seed, rep, kPhiloxRounds, moore ? 8 : 4, nullptr, mcs0, n, ref.data(), rc.data());
   uint32_t seen = 0, want = 0;
-  for (uint32_t i = 0; i < nw; ++i) seen |= species_bits(reinterpret_cast<const uint2 *>(src)[i]);
+  for (uint32_t i = 0; i < nw; ++i) seen |= species_fold<SP == 8>(species_bits<SP == 8>(reinterpret_cast<const uint2 *>(src)[i]));
   for (uint8_t v : ref) want |= 1u << v;
   const bool ok = out == ref && ((seen ^ want) & ~1u) == 0 && sm.front() == 0x1F1F1F1F1F1F1F1Full && sm.back() == sm.front();
   if (!ok) printf("MISMATCH L=%u S=%u slots=%d threads=%u\n", L, S, kSlots, nt);
@@ -88,7 +88,7 @@ static int window_case(uint32_t stop) {
     if (n == 1) break;
     t -= n; replay = true;
   }
-  const bool ok = t == stop && run <= stop + 2 * (stop / 16) && tests <= 130 + stop / 16 + 32 && (stop > 128 || run == stop);
+  const bool ok = t == stop && run <= stop + stop / 8 && tests <= 137 + stop / 32 + 32 && (stop > 128 || run == stop);
   if (!ok) printf("WINDOWS stop=%u run=%u tests=%u\n", stop, run, tests);
   return !ok;
 }

@@ -52,15 +52,15 @@ def test_early_stops_cost_no_more_than_testing_every_mcs(L, n):
 
 
 @pytest.mark.parametrize("S", [3, 9])
-@pytest.mark.parametrize("L,sel", [(90, 0.06), (98, 0.02), (126, 0.03),
-                                   (222, 0.04)])
+@pytest.mark.parametrize("L,sel", [(90, 0.025), (98, 0.02), (126, 0.02),
+                                   (222, 0.02)])
 def test_stops_inside_a_window(L, S, sel):
     p, j = pair(L, S, None, 0.5, sel, 1.0, seed=5, replica=L, D=takeover(S),
                 route="lds")
     g0 = j.init()
     full = oracle_until(j, g0.copy(), 3, 3000, escg.STOP_FIRST_EXTINCTION)
     t = int(full[1])
-    assert full[0] == 1 and t > 144, full
+    assert full[0] == 1 and t > 257, full
     for cap in (t - 1, t, t + 1, 3000):
         ref = g0.copy()
         r = oracle_until(j, ref, 3, cap, escg.STOP_FIRST_EXTINCTION)
@@ -92,4 +92,4 @@ def test_batch_stops_inside_windows(init, mode):
         stops.append(int(ref[1]))
         assert np.array_equal(rr[:6], ref), (p.L, rr, ref)
         assert np.array_equal(lat, g), p.L
-    assert sum(144 < t < 2500 for t in stops) >= 3, stops
+    assert sum(257 < t < 2500 for t in stops) >= 3, stops
