@@ -79,16 +79,17 @@ typedef int32_t escg_status;
  * patches would be too large). */
 /* Launches that wait.  The workgroups of a persistent launch (single job or
  * several) wait for each other's halos, never for other work.  Each such
- * launch holds no more workgroups than the device keeps resident and is made
- * cooperatively: HIP runs a process's cooperative launches on a device one
- * at a time, whatever their streams, so calls on different streams may
- * overlap freely, and a launch becomes resident as the kernels that hold CUs
- * (none of which waits) end.  Not covered: launches replayed from captured
- * graphs; replay graphs that hold such calls on one stream, and not beside
- * such calls on another.  A wait that exceeds its bound all the same
- * (seconds; another process's waiting launches on the same device, say)
- * leaves the lattice invalid and is reported as ESCG_ETIMEOUT by
- * escg_async_status or by the call. */
+ * launch holds no more workgroups than the device keeps resident, and the
+ * library runs a process's launches of this kind on a device one at a time,
+ * whatever their streams and host threads (single jobs' launches are
+ * cooperative, which HIP orders; multi-job launches are ordered by an event),
+ * so calls on different streams may overlap freely; a launch becomes resident
+ * as the kernels that hold CUs (none of which waits) end.  Not covered:
+ * launches replayed from captured graphs; replay graphs that hold such calls
+ * on one stream, and not beside such calls on another.  A wait that exceeds
+ * its bound all the same (seconds; another process's waiting launches on the
+ * same device, say) leaves the lattice invalid and is reported as
+ * ESCG_ETIMEOUT by escg_async_status or by the call. */
 #define ESCG_ROUTE_LDS        1u
 #define ESCG_ROUTE_TILED      2u
 #define ESCG_ROUTE_PERSISTENT 3u

@@ -2491,6 +2491,66 @@ void launch_step(const StepArgs &a, const TiledPlan &sp, bool small,
     (void)hipLaunchKernel(fn, dim3(T), dim3(sp.threads), args, sp.lds, st);
 }
 
+bool stream_captures(hipStream_t st)
+{
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &cs) != hipSuccess)
+        (void)hipGetLastError();
+    return cs != hipStreamCaptureStatusNone;
+}
+
+// A launch whose workgroups wait for each other (no more of them than the
+// device keeps resident).  Two such launches must not run side by side, each
+// resident in part and holding the CUs that the other waits for.  The runtime
+// runs cooperative launches one at a time on a device (measured with four
+// workgroups each: one 17.4 ms, two on two streams 35.1; ordinary launches
+// overlap), but one costs some 30 us more to get going, 4 % of a multi-job
+// launch of 25 MCS.  So multi-job launches (`multi`) are ordinary ones, ordered
+// by an event per device: each waits for the waiting launch before it, and each
+// later one for it.  Single-job launches take part once there has been a
+// multi-job launch; the first of those is cooperative, and so after all single
+// ones before it.  Captured launches are not ordered (escg.h says so).
+hipError_t launch_waiting(const void *fn, uint32_t grid, uint32_t block,
+                          void **args, size_t lds, hipStream_t st, bool multi)
+{
+    struct Order {
+        std::mutex mu;
+        hipEvent_t last = nullptr; // after the last launch that takes part
+    };
+    static std::mutex mu;
+    static std::map<int, Order> *const orders = new std::map<int, Order>;
+    int dev = 0;
+    (void)hipGetDevice(&dev);
+    Order *o;
+    {
+        std::lock_guard<std::mutex> lk(mu);
+        o = &(*orders)[dev];
+    }
+    const bool captured = stream_captures(st);
+    std::lock_guard<std::mutex> lk(o->mu);
+    bool ordered = false;
+    if (!captured && o->last) {
+        ordered = hipStreamWaitEvent(st, o->last, 0) == hipSuccess;
+        if (!ordered)
+            (void)hipGetLastError();
+    }
+    const hipError_t e =
+        multi && ordered
+            ? hipLaunchKernel(fn, dim3(grid), dim3(block), args, lds, st)
+            : hipLaunchCooperativeKernel(fn, dim3(grid), dim3(block), args,
+                                         (unsigned)lds, st);
+    if (e == hipSuccess && !captured && multi && !o->last &&
+        hipEventCreateWithFlags(&o->last, hipEventDisableTiming) !=
+            hipSuccess) { // the next multi-job launch is cooperative as well
+        (void)hipGetLastError();
+        o->last = nullptr;
+    }
+    if (e == hipSuccess && !captured && o->last &&
+        hipEventRecord(o->last, st) != hipSuccess)
+        (void)hipGetLastError(); // the caller's synchronisation reports it
+    return e;
+}
+
 // Runs n_mcs MCS of a large lattice with the persistent kernel.  Returns
 // ESCG_EUNSUPPORTED (nothing enqueued) if no plan fits or the cooperative
 // launch is refused; the caller then uses the per-MCS tiled kernel.
@@ -2547,8 +2607,8 @@ escg_status run_tiled_persistent(const escg_params *p, const Derived &d,
     void *args[] = {&a};
     const void *fn = persistent_kernel(d.small, d.prob, plan.list);
     allow_dynamic_lds(fn, plan.lds);
-    hipError_t e = hipLaunchCooperativeKernel(fn, dim3(T), dim3(plan.threads),
-                                              args, (unsigned)plan.lds, st);
+    const hipError_t e =
+        launch_waiting(fn, T, plan.threads, args, plan.lds, st, false);
     escg_status s = ESCG_OK;
     if (e != hipSuccess) {
         std::snprintf(g_last_error, sizeof(g_last_error),
@@ -2793,8 +2853,8 @@ escg_status run_patch(const escg_params *p, const Derived &d,
     if (alone)
         return last_hip(hipLaunchKernel(fn, dim3(T), dim3(nt), args, plan.lds,
                                         st));
-    const hipError_t e = hipLaunchCooperativeKernel(
-        fn, dim3(T), dim3(nt), args, (unsigned)plan.lds, st);
+    const hipError_t e =
+        launch_waiting(fn, T, nt, args, plan.lds, st, false);
     if (e != hipSuccess) {
         std::snprintf(g_last_error, sizeof(g_last_error),
                       "cooperative launch of %u x %u refused: %s", T, nt,
@@ -3390,14 +3450,8 @@ escg_status launch_multi(std::vector<uint32_t> idx,
         const TiledArgs *tp = reinterpret_cast<const TiledArgs *>(dev);
         uint32_t nj = m;
         void *args[] = {&tp, &nj};
-        // cooperative, as every launch whose workgroups wait for each other:
-        // the runtime runs such launches one at a time on a device, so that
-        // two on different streams never hold CUs that the other waits for
-        // (measured with four workgroups each: one 17.4 ms, two on two
-        // streams 35.1; ordinary launches overlap).  24 jobs take 9.41 ms
-        // either way.
-        const hipError_t e = hipLaunchCooperativeKernel(
-            fn, dim3(wg), dim3(kMultiThreads), args, (unsigned)lds, st);
+        const hipError_t e = launch_waiting(fn, wg, kMultiThreads, args, lds,
+                                            st, true);
         if (e != hipSuccess) {
             std::snprintf(g_last_error, sizeof(g_last_error),
                           "cooperative launch of %u x %u refused: %s", wg,
@@ -3507,17 +3561,11 @@ Route choose_route(const escg_params *p, hipStream_t st, bool until)
     const uint32_t L = p->L, S = p->S;
     const bool fits_lds = L <= lds_max_L(S);
     const auto tiles_ok = [&] { return plan_tiled(L, S, plan_hints(p)).ok; };
-    const auto capturing = [&] {
-        hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-        if (hipStreamIsCapturing(st, &cs) != hipSuccess)
-            (void)hipGetLastError();
-        return cs != hipStreamCaptureStatusNone;
-    };
     const auto resident_ok = [&] {
         if ((L & 7u) == 0 ? L < kPersistentMinL
                           : L <= kWholeMaxL || (until && fits_lds))
             return false;
-        return plan_resident(p).ok() && (!capturing() || tiles_ok());
+        return plan_resident(p).ok() && (!stream_captures(st) || tiles_ok());
     };
     switch (p->launch.route) {
     case ESCG_ROUTE_LDS:

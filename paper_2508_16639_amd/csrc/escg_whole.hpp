@@ -235,7 +235,7 @@ __device__ __forceinline__ void whole_pass_slots(
 // eighth.
 // Batches that stop after 25 MCS (64 of L = 256, 512 of L = 192, 16 of L = 8),
 // us: first test after 32 MCS 1048, 3177, 349; in-place kernel, which tests
-// after every MCS, 789, 2447, 223; now 631, 2445, 192.
+// after every MCS, 775, 2463, 225; now 639, 2470, 194.
 __host__ __device__ inline uint32_t pair_window(uint32_t t)
 {
     return t < 128u ? 1u : min(32u, t / 8u);

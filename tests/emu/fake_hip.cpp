@@ -120,6 +120,23 @@ const char *hipGetErrorName(hipError_t) { return "hipErrorFake"; }
 const char *hipGetErrorString(hipError_t) { return "fake error"; }
 hipError_t hipDeviceSynchronize() { return hipSuccess; }
 hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
+// events: recorded among the launches, the event's number as their grid
+hipError_t hipEventCreateWithFlags(hipEvent_t *e, unsigned)
+{
+    static uintptr_t events = 0;
+    *e = reinterpret_cast<hipEvent_t>(++events);
+    return hipSuccess;
+}
+hipError_t hipEventRecord(hipEvent_t e, hipStream_t)
+{
+    launches.push_back({"event record", 0, (uint32_t)(uintptr_t)e, 0, 0});
+    return hipSuccess;
+}
+hipError_t hipStreamWaitEvent(hipStream_t, hipEvent_t e, unsigned)
+{
+    launches.push_back({"event wait", 0, (uint32_t)(uintptr_t)e, 0, 0});
+    return hipSuccess;
+}
 hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus *s)
 {
     *s = capturing ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone;

@@ -40,47 +40,76 @@ WAITING = ("patch_kernel", "tiled_persistent_kernel",
 
 
 def waiting_launches(f):
-    """Launches whose workgroups wait for each other are cooperative (ordered
-    against each other by the runtime) and fit the device; the others are
-    ordinary."""
+    """Launches whose workgroups wait for each other fit the device and never
+    run side by side: single jobs' are cooperative (ordered by the runtime), so
+    is the first multi-job launch; later multi-job launches are ordinary and
+    wait for the event of the waiting launch before them, which every such
+    launch then records and waits for.  Other launches are ordinary."""
     def check(*kinds):
-        for x in f.launches():
+        log = f.launches()
+        for x in log:
             waits = any(k in x.name for k in WAITING)
-            assert x.cooperative == waits, x
             assert not waits or x.grid <= 256, x
+            if "multi" not in x.name:
+                assert x.cooperative == waits, x
         for k in kinds:
-            assert f.names(k), (k, f.launches())
+            assert f.names(k), (k, log)
+        return [x for x in log
+                if "event" in x.name or any(k in x.name for k in WAITING)]
 
-    f.reset()
-    for p in (f.params(300), f.params(512), f.params(3200, S=9),
-              f.params(3600), f.params(512, tile=(32, 32))):
-        assert f.step(p, 50) == 0
-    check("patch_kernel", "tiled_persistent_kernel")
-    for wgs in (0, 40):
+    def singles():
+        f.reset()
+        for p in (f.params(300), f.params(512), f.params(3200, S=9),
+                  f.params(3600), f.params(512, tile=(32, 32))):
+            assert f.step(p, 50) == 0
+        return check("patch_kernel", "tiled_persistent_kernel")
+
+    def batch(wgs):
         f.reset()
         ps = [f.params(400 << (j % 3), S=(3, 9)[j % 2]) for j in range(24)]
         ps[0] = ps[0].with_launch(max_wgs=wgs)
         assert f.step_batch(ps, [500] * 24) == 0
         assert f.lib.escg_last_route() == f.escg.ROUTE_PERSISTENT
-        check("tiled_persistent_multi_kernel")
-        assert not wgs or all(x.grid <= wgs for x in f.names("multi"))
+        assert not wgs or all(x.grid <= wgs for x in f.names("multi_kernel"))
+        return check("tiled_persistent_multi_kernel")
+
+    def in_chain(log):
+        for k in range(0, len(log), 3):
+            wait, run, record = log[k:k + 3]
+            assert (wait.name, record.name) == ("event wait", "event record")
+            assert wait.grid == record.grid == 1
+            assert run.cooperative == ("multi" not in run.name)
+
+    assert all(x.cooperative for x in singles())
+    first = batch(0)
+    assert first[0].cooperative and first[1].name == "event record"
+    in_chain(first[2:])
+    assert len(first) > 2
+    in_chain(singles())
+    in_chain(batch(40))
+    # under capture: no events, cooperative
+    f.reset(capture=True)
+    assert f.step(f.params(512), 50) == 0
+    assert f.step_batch([f.params(400)] * 2, [5, 5]) == 0
+    log = check()
+    assert len(log) == 2 and all(x.cooperative for x in log)
 
 
 def refused_multi(f, refuse):
     """Jobs of a refused multi-job launch go out per MCS, all of their MCS;
     the launches before it stay."""
-    f.reset(refuse=refuse)
     # S <= 7 and S > 7: two launches
+    f.reset(refuse=refuse, capture=True)  # all of them cooperative
     ps = [f.params(400), f.params(136, S=9), f.params(800)]
     assert f.step_batch(ps, [6, 5, 4]) == 0
-    assert len(f.names("multi")) == refuse
+    assert len(f.names("multi_kernel")) == refuse
     steps = f.names("tiled_step_batch_kernel")
     assert len(steps) == {0: 11, 1: 6, 2: 0}[refuse], steps
     assert f.lib.escg_last_route() == (f.escg.ROUTE_PERSISTENT if refuse
                                        else f.escg.ROUTE_TILED)
 
 
-def test_launches_that_wait_are_cooperative(fake_so):
+def test_launches_that_wait_never_run_side_by_side(fake_so):
     fake_hip.run(fake_so, __file__, "waiting_launches")
 
 
