@@ -236,14 +236,14 @@ escg_status escg_step_mcs(const escg_params *p, uint8_t *d_lattice,
  * computation as escg_step_mcs, with the same arguments, results (byte for
  * byte), routing and launch choices, but the call allocates nothing.  Every
  * scratch buffer it needs (the persistent kernel's exchange area and abort
- * word, the tiled path's ping-pong lattice, the selection thresholds of
- * dominance probabilities) is carved from one file-scope device array of
+ * word or, for a few MCS, its copy of the lattice, the tiled path's ping-pong
+ * lattice, the selection thresholds of dominance probabilities) is carved from one file-scope device array of
  * ESCG_STATIC_SCRATCH_BYTES bytes per GPU, which the library holds until the
  * process ends.  A call that would need more returns ESCG_ENOMEM with
  * nothing enqueued and escg_last_error() giving the bytes needed (the
- * tiled path takes L*L bytes, the persistent path max(exchange
- * area, L*L), dominance probabilities 8 KiB more: every L <= 8184 fits).  Calls on one GPU share its
- * array and each call initialises what it uses, so calls whose work
+ * tiled path takes L*L bytes, the persistent path at most max(exchange area,
+ * L*L), dominance probabilities 8 KiB more: every L <= 8184 fits).  Calls on
+ * one GPU share its array and each call initialises what it uses, so calls whose work
  * overlaps on the device (different streams, or different host threads)
  * race on it and give undefined results: serialise them. */
 #define ESCG_STATIC_SCRATCH_BYTES (64u << 20)

@@ -30,3 +30,24 @@ def test_largest_sides(L, S, K):
         lats, rr = _batch([(p, j, cap, None)], mode, True, [3])
         assert np.array_equal(rr[0][:S + 3], r)
         assert np.array_equal(lats[0], g)
+
+
+@pytest.mark.parametrize("sides", [(2, 4, 8, 6), (10, 16, 2, 14), (24, 18, 8),
+                                   (34, 30, 2), (46, 48, 64), (72, 70, 6)])
+@pytest.mark.parametrize("S,K", [(3, [1]), (9, [1, 2, 4])])
+def test_small_batches(sides, S, K):
+    """Workgroups of as many waves as the largest lattice has quads for."""
+    for mode in (escg.STOP_FIRST_EXTINCTION, escg.STOP_MONOCULTURE,
+                 escg.STOP_NONE):
+        jobs = []
+        for i in range(3 * len(sides)):
+            L = sides[i % len(sides)]
+            p, j = pair(L, S, K, [0.5, 4.0, 0.0][i % 3], seed=5, replica=i,
+                        moore=i % 2 == 1)
+            jobs.append((p, j, [300, 40, 0, 1][i % 4], None))
+        lats, r = _batch(jobs, mode, True, [i for i in range(len(jobs))])
+        for i, ((p, j, cap, _), lat, rr) in enumerate(zip(jobs, lats, r)):
+            g = j.init()
+            want = oracle_until(j, g, i, cap, mode)
+            assert np.array_equal(rr[:S + 3], want), (p.L, cap, rr, want)
+            assert np.array_equal(lat, g), (p.L, cap)
