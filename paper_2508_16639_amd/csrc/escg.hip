@@ -2505,17 +2505,19 @@ bool stream_captures(hipStream_t st)
 // runs cooperative launches one at a time on a device (measured with four
 // workgroups each: one 17.4 ms, two on two streams 35.1; ordinary launches
 // overlap), but one costs some 30 us more to get going, 4 % of a multi-job
-// launch of 25 MCS.  So multi-job launches (`multi`) are ordinary ones, ordered
-// by an event per device: each waits for the waiting launch before it, and each
-// later one for it.  Single-job launches take part once there has been a
-// multi-job launch; the first of those is cooperative, and so after all single
-// ones before it.  Captured launches are not ordered (escg.h says so).
+// launch of 25 MCS.  So of launches that follow each other, multi-job ones
+// (`multi`) are ordinary, each recording a device's event that the next one, on
+// whatever stream, waits for.  Single jobs' launches are cooperative and wait
+// for the event too; after them a multi-job launch is cooperative, and so
+// behind them.  (Recording the event after single launches as well cost a step
+// 5 us.)  Captured launches are not ordered (escg.h says so).
 hipError_t launch_waiting(const void *fn, uint32_t grid, uint32_t block,
                           void **args, size_t lds, hipStream_t st, bool multi)
 {
     struct Order {
         std::mutex mu;
-        hipEvent_t last = nullptr; // after the last launch that takes part
+        hipEvent_t last = nullptr; // after the last multi-job launch
+        bool single = true;        // single launches may have followed it
     };
     static std::mutex mu;
     static std::map<int, Order> *const orders = new std::map<int, Order>;
@@ -2526,27 +2528,36 @@ hipError_t launch_waiting(const void *fn, uint32_t grid, uint32_t block,
         std::lock_guard<std::mutex> lk(mu);
         o = &(*orders)[dev];
     }
-    const bool captured = stream_captures(st);
+    if (stream_captures(st))
+        return hipLaunchCooperativeKernel(fn, dim3(grid), dim3(block), args,
+                                          (unsigned)lds, st);
     std::lock_guard<std::mutex> lk(o->mu);
-    bool ordered = false;
-    if (!captured && o->last) {
-        ordered = hipStreamWaitEvent(st, o->last, 0) == hipSuccess;
-        if (!ordered)
-            (void)hipGetLastError();
+    if (o->last) {
+        const hipError_t e = hipStreamWaitEvent(st, o->last, 0);
+        if (e != hipSuccess)
+            return e;
+    }
+    if (!multi) {
+        o->single = true;
+        return hipLaunchCooperativeKernel(fn, dim3(grid), dim3(block), args,
+                                          (unsigned)lds, st);
+    }
+    if (!o->last) {
+        const hipError_t e =
+            hipEventCreateWithFlags(&o->last, hipEventDisableTiming);
+        if (e != hipSuccess) {
+            o->last = nullptr;
+            return e;
+        }
     }
     const hipError_t e =
-        multi && ordered
-            ? hipLaunchKernel(fn, dim3(grid), dim3(block), args, lds, st)
-            : hipLaunchCooperativeKernel(fn, dim3(grid), dim3(block), args,
-                                         (unsigned)lds, st);
-    if (e == hipSuccess && !captured && multi && !o->last &&
-        hipEventCreateWithFlags(&o->last, hipEventDisableTiming) !=
-            hipSuccess) { // the next multi-job launch is cooperative as well
-        (void)hipGetLastError();
-        o->last = nullptr;
-    }
-    if (e == hipSuccess && !captured && o->last &&
-        hipEventRecord(o->last, st) != hipSuccess)
+        o->single ? hipLaunchCooperativeKernel(fn, dim3(grid), dim3(block),
+                                               args, (unsigned)lds, st)
+                  : hipLaunchKernel(fn, dim3(grid), dim3(block), args, lds, st);
+    if (e != hipSuccess)
+        return e;
+    o->single = false;
+    if (hipEventRecord(o->last, st) != hipSuccess)
         (void)hipGetLastError(); // the caller's synchronisation reports it
     return e;
 }

@@ -41,10 +41,10 @@ WAITING = ("patch_kernel", "tiled_persistent_kernel",
 
 def waiting_launches(f):
     """Launches whose workgroups wait for each other fit the device and never
-    run side by side: single jobs' are cooperative (ordered by the runtime), so
-    is the first multi-job launch; later multi-job launches are ordinary and
-    wait for the event of the waiting launch before them, which every such
-    launch then records and waits for.  Other launches are ordinary."""
+    run side by side: single jobs' are cooperative (ordered by the runtime),
+    and so is a multi-job launch after them; one after another multi-job launch
+    is ordinary.  All wait for the event that a multi-job launch records.
+    Other launches are ordinary."""
     def check(*kinds):
         log = f.launches()
         for x in log:
@@ -73,20 +73,22 @@ def waiting_launches(f):
         assert not wgs or all(x.grid <= wgs for x in f.names("multi_kernel"))
         return check("tiled_persistent_multi_kernel")
 
-    def in_chain(log):
-        for k in range(0, len(log), 3):
-            wait, run, record = log[k:k + 3]
-            assert (wait.name, record.name) == ("event wait", "event record")
-            assert wait.grid == record.grid == 1
-            assert run.cooperative == ("multi" not in run.name)
+    def kinds(log):
+        """w: wait, r: record, C / S: cooperative multi-job / single launch,
+        M: ordinary multi-job launch."""
+        assert all(x.grid == 1 for x in log if "event" in x.name)
+        return "".join(
+            "w" if x.name == "event wait" else "r" if "event" in x.name else
+            "S" if "multi" not in x.name else "C" if x.cooperative else "M"
+            for x in log)
 
-    assert all(x.cooperative for x in singles())
-    first = batch(0)
-    assert first[0].cooperative and first[1].name == "event record"
-    in_chain(first[2:])
-    assert len(first) > 2
-    in_chain(singles())
-    in_chain(batch(40))
+    n = kinds(singles())
+    assert set(n) == {"S"}
+    first = kinds(batch(0))  # two launches or more: S <= 7 and S > 7
+    assert first == "Cr" + "wMr" * (len(first) // 3) and len(first) > 2
+    assert kinds(batch(40)).replace("wMr", "") == ""
+    assert kinds(singles()) == "wS" * len(n)
+    assert kinds(batch(0)) == "wCr" + "wMr" * (len(first) // 3)
     # under capture: no events, cooperative
     f.reset(capture=True)
     assert f.step(f.params(512), 50) == 0
